@@ -47,9 +47,12 @@ extern "C" {
 #define DC_ERR_DEGENERATE (-5) /* a frame's total surface area is zero or not finite */
 #define DC_ERR_UNSUPPORTED (-6)/* a valid request the library cannot run (serving program) */
 
-/* precision of the all-pairs nearest-neighbour search (both give the same indices) */
+/* precision of the nearest-neighbour search (both give the same indices and distances).  Either
+ * searches spatially ordered clouds, ruling most pairs out by bounding boxes, wherever that is the
+ * faster way; elsewhere every pair is evaluated as below. */
 #define DC_PREC_FP32 0        /* exact single-precision search on the vector ALUs */
-#define DC_PREC_BF16_REFINE 1 /* bf16 matrix-core screen, certified, exact fp32 re-evaluation */
+#define DC_PREC_BF16_REFINE 1 /* bf16 matrix-core screen, certified, exact fp32 re-evaluation, where
+                               * it is faster than the exact search */
 
 /* reduction of the two directions into the per-frame loss */
 #define DC_RED_BIDIR_MEAN 0   /* Eq. 1: mean over a of min_b + mean over b of min_a */
@@ -187,7 +190,7 @@ int dc_sample_surface_bwd(dc_ctx *ctx, const float *grad_points, const int32_t *
  * ties going to the smallest index; dist_* hold that float d.  The loss sums the float distances
  * in double.
  * Errors: DC_ERR_INVALID (also: only one of dist_b / idx_b NULL, or NULL with Eq. 1), DC_ERR_HIP,
- * DC_ERR_NOMEM, DC_ERR_BUDGET. */
+ * DC_ERR_NOMEM, DC_ERR_BUDGET (no search's scratch fits the budget). */
 int dc_chamfer_fwd(dc_ctx *ctx, const float *a, const float *b, int T, int Na, int Nb,
                    int precision, int reduction, const float *frame_w, float *dist_a,
                    int32_t *idx_a, float *dist_b, int32_t *idx_b, double *loss, void *stream);
@@ -232,10 +235,11 @@ int dc_rigid_pose_bwd(dc_ctx *ctx, const double *q, const float *p0, const int32
                       const float *grad_verts, int T, int B, int V, double *grad_q,
                       void *stream);
 
-/* Counters of the bf16 screen since the context was created (read after dc_sync):
- *   queries    nearest-neighbour queries answered by the screened search
- *   candidates candidate groups re-evaluated exactly
- *   fallbacks  queries whose certificate failed and that were searched exhaustively */
+/* Counters of the DC_PREC_BF16_REFINE searches since the context was created (read after dc_sync):
+ *   queries    nearest-neighbour queries answered by the ordered or the screened search
+ *   candidates candidate groups re-evaluated exactly (ordered: the 16 points around the minimum)
+ *   fallbacks  queries searched a second time: whose certificate failed (screen), or whose minimum
+ *              was met in more than one group (ordered) */
 typedef struct dc_stats {
     uint64_t queries;
     uint64_t candidates;
@@ -246,8 +250,8 @@ int dc_get_stats(dc_ctx *ctx, dc_stats *out);
 /* ------------------------------------------------------------------ kernel timing */
 /* With profiling on, the direct calls bracket their kernels with HIP events on the caller's
  * stream and accumulate the elapsed device time per category:
- *   [0] the all-pairs nearest-neighbour kernel (exact fp32 search, or the bf16 screen)
- *   [1] the exact re-evaluation of screened candidates
+ *   [0] the nearest-neighbour kernel (over ordered clouds, exact fp32 search, or bf16 screen)
+ *   [1] the ordering of the clouds, or the exact re-evaluation of screened candidates
  *   [2] sampling (areas, CDF, face choice, points)
  *   [3] the backward kernels (Chamfer and sampling backward, their sorts)
  * dc_get_kernel_times waits for the recorded events, returns the sums and launch counts, and

@@ -15,7 +15,7 @@ CSRC = os.path.join(HERE, "csrc")
 BUILD = os.path.join(os.path.dirname(HERE), "_build")
 LIB = os.path.join(HERE, "libdiffcloud.so")
 
-SOURCES = ["abi.hip", "sample.hip", "nn_exact.hip", "screen.hip", "segsort.hip", "backward.hip",
+SOURCES = ["abi.hip", "sample.hip", "nn_exact.hip", "screen.hip", "ordered.hip", "segsort.hip", "backward.hip",
            "rigid.hip", "scheduler.hip", "noalloc.hip"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")

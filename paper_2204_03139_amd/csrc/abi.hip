@@ -160,18 +160,36 @@ int enqueue_sample(dc_ctx *prof, const float *verts, const int32_t *faces, int T
     return launched("sample_surface launch");
 }
 
-size_t chamfer_fwd_scratch_bytes(int T, int Na, int Nb, int precision) {
-    if (precision == DC_PREC_BF16_REFINE) return screen_scratch_bytes(T, Na, Nb);
+size_t search_scratch_bytes(Search search, int T, int Na, int Nb) {
+    if (search == Search::ordered) return ordered_scratch_bytes(T, Na, Nb);
+    if (search == Search::screen) return screen_scratch_bytes(T, Na, Nb);
     return std::max({nn_exact_scratch_bytes(T, Na, Nb), nn_exact_scratch_bytes(T, Nb, Na),
                      nn_bidir_scratch_bytes(T, Na, Nb)});
 }
 
+// The search over ordered clouds wherever it is the faster one (ordered_pays), in either precision.
+// Of the other calls, the bf16 ones keep the screen where it is still the faster: one to a few
+// frames of many rows against a handful of targets (one frame of 32,768 x 64: 103 us against 145 us
+// for the exact search and 129 us for the ordered one; 32 frames: 317 against 106 us), and where
+// the exact search would need more scratch.
+Search plan_search(int T, int Na, int Nb, int precision, bool two, bool ordering) {
+    if (ordering && ordered_pays(T, Na, Nb, two)) return Search::ordered;
+    if (precision == DC_PREC_BF16_REFINE &&
+        ((Na >= 8192 && (long)T * Na <= 65536) ||
+         search_scratch_bytes(Search::exact, T, Na, Nb) > screen_scratch_bytes(T, Na, Nb)))
+        return Search::screen;
+    return Search::exact;
+}
+
 int enqueue_chamfer_fwd(dc_ctx *prof, const float *a, const float *b, int T, int Na, int Nb,
-                        int precision, int reduction, const float *frame_w, float *dist_a,
-                        int32_t *idx_a, float *dist_b, int32_t *idx_b, double *loss,
+                        Search search, bool count, int reduction, const float *frame_w,
+                        float *dist_a, int32_t *idx_a, float *dist_b, int32_t *idx_b, double *loss,
                         char *scratch, unsigned long long *stats, hipStream_t s) {
+    if (!count) stats = nullptr;
     // idx_b == NULL: the unidirectional loss (Eq. 2) needs only the a -> b direction
-    if (precision == DC_PREC_BF16_REFINE) {
+    if (search == Search::ordered) {
+        launch_ordered(a, Na, b, Nb, T, idx_a, dist_a, idx_b, dist_b, scratch, stats, prof, s);
+    } else if (search == Search::screen) {
         launch_chamfer_screened(a, Na, b, Nb, T, idx_a, dist_a, idx_b, dist_b, scratch, stats,
                                 prof, s);
     } else {
@@ -471,12 +489,21 @@ int dc_chamfer_fwd(dc_ctx *ctx, const float *a, const float *b, int T, int Na, i
     if (rc) return rc;
     DC_HIP(hipSetDevice(ctx->device));
     std::lock_guard<std::mutex> g(ctx->mu);
-    const size_t need = chamfer_fwd_scratch_bytes(T, Na, Nb, precision);
+    Search search = plan_search(T, Na, Nb, precision, idx_b != nullptr, true);
+    size_t need = search_scratch_bytes(search, T, Na, Nb);
     rc = arena_reserve(ctx, need, static_cast<hipStream_t>(stream));
+    if (rc == DC_ERR_BUDGET && search == Search::ordered) {
+        // the exact search may need less than the ordered clouds
+        search = plan_search(T, Na, Nb, precision, idx_b != nullptr, false);
+        need = search_scratch_bytes(search, T, Na, Nb);
+        clear_error();
+        rc = arena_reserve(ctx, need, static_cast<hipStream_t>(stream));
+    }
     if (rc) return rc;
     ArenaUse use{ctx, static_cast<hipStream_t>(stream)};
-    return enqueue_chamfer_fwd(ctx, a, b, T, Na, Nb, precision, reduction, frame_w, dist_a, idx_a,
-                               dist_b, idx_b, loss, ctx->arena.take<char>(need), ctx->d_stats,
+    return enqueue_chamfer_fwd(ctx, a, b, T, Na, Nb, search, precision == DC_PREC_BF16_REFINE,
+                               reduction, frame_w, dist_a, idx_a, dist_b, idx_b, loss,
+                               ctx->arena.take<char>(need), ctx->d_stats,
                                static_cast<hipStream_t>(stream));
 }
 
@@ -562,7 +589,7 @@ int dc_request_bytes(const dc_request *req, int want_grad, size_t *bytes) {
         return DC_ERR_INVALID;
     }
     *bytes = request_bytes(req->T, req->V, req->F, req->n_sim, req->n_obs, req->precision,
-                           want_grad != 0);
+                           req->reduction, want_grad != 0);
     return DC_OK;
 }
 

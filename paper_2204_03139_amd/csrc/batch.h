@@ -86,6 +86,13 @@ enum KernelType : int {
     KT_BIDIR4,
     KT_BIDIR_MERGE,
     KT_SS_SMALL,
+    KT_ORDER_SMALL,
+    KT_ORDER_COUNT,
+    KT_ORDER_SCAN,
+    KT_ORDER_DEAL,
+    KT_ORDER_BOX,
+    KT_NEAR,
+    KT_NEAR_SHARED,
     KT_COUNT
 };
 
@@ -98,9 +105,9 @@ struct OpRec {
     alignas(16) unsigned char p[OP_PARAM_BYTES];
 };
 
-constexpr int MAX_STAGES = 72;   // length of the serving program
+constexpr int MAX_STAGES = 80;   // length of the serving program
 constexpr int MAX_BATCH = 32;    // requests per batch
-constexpr int MAX_OPS = MAX_STAGES * MAX_BATCH;
+constexpr int MAX_OPS = 72 * MAX_BATCH - 1;
 
 struct StageHdr {
     int total;  // flattened workgroups of the stage over the batch
@@ -214,6 +221,7 @@ BatchedKernel batched_kernel() {
 void register_sample_kernels(BatchedKernel *table);
 void register_nn_kernels(BatchedKernel *table);
 void register_screen_kernels(BatchedKernel *table);
+void register_ordered_kernels(BatchedKernel *table);
 void register_sort_kernels(BatchedKernel *table);
 void register_backward_kernels(BatchedKernel *table);
 void register_fill_kernels(BatchedKernel *table);

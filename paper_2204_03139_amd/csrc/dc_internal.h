@@ -155,6 +155,14 @@ void launch_chamfer_screened(const float *a, int Na, const float *b, int Nb, int
                              char *scratch, unsigned long long *stats, dc_ctx *prof,
                              hipStream_t s);
 
+// the same search over spatially ordered clouds, most pairs ruled out by bounding boxes; idx_b NULL:
+// only the neighbours of a
+bool ordered_pays(int T, int Na, int Nb, bool two);
+size_t ordered_scratch_bytes(int T, int Na, int Nb);
+void launch_ordered(const float *a, int Na, const float *b, int Nb, int T, int32_t *idx_a,
+                    float *dist_a, int32_t *idx_b, float *dist_b, char *scratch,
+                    unsigned long long *stats, dc_ctx *prof, hipStream_t s);
+
 // per-frame loss from the float distances, accumulated in double
 void launch_loss(const float *dist_a, const float *dist_b, int T, int Na, int Nb, int reduction,
                  const float *frame_w, double *loss, hipStream_t s);
@@ -196,9 +204,14 @@ int enqueue_sample(dc_ctx *prof, const float *verts, const int32_t *faces, int T
                    int N, uint64_t seed, const uint32_t *uniforms, const uint8_t *mask,
                    int mask_per_frame, float *points, int32_t *face_idx, float *bary, Arena &ar,
                    unsigned *status, hipStream_t s);
-size_t chamfer_fwd_scratch_bytes(int T, int Na, int Nb, int precision);
+// The nearest-neighbour search of a call (all give the same results), and its scratch.  `two`: both
+// directions are wanted; `ordering`: whether the search over ordered clouds may be chosen (its
+// scratch can be larger than the exact search's).
+enum class Search { ordered, screen, exact };
+Search plan_search(int T, int Na, int Nb, int precision, bool two, bool ordering);
+size_t search_scratch_bytes(Search search, int T, int Na, int Nb);
 int enqueue_chamfer_fwd(dc_ctx *prof, const float *a, const float *b, int T, int Na, int Nb,
-                        int precision,
+                        Search search, bool count,
                         int reduction, const float *frame_w, float *dist_a, int32_t *idx_a,
                         float *dist_b, int32_t *idx_b, double *loss, char *scratch,
                         unsigned long long *stats, hipStream_t s);

@@ -11,6 +11,7 @@ int sched_wait(dc_ctx *ctx, uint64_t ticket, long long timeout_us);
 void sched_destroy(dc_ctx *ctx);
 
 // device bytes a request holds while admitted (inputs, intermediates, outputs, scratch)
-size_t request_bytes(int T, int V, int F, int Na, int Nb, int precision, bool want_grad);
+size_t request_bytes(int T, int V, int F, int Na, int Nb, int precision, int reduction,
+                     bool want_grad);
 
 }  // namespace dc

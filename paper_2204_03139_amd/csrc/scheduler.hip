@@ -108,6 +108,8 @@ void fill_f64(double *p, int n, double v, hipStream_t s) {
         KT_SS_HIST, KT_SS_SCAN, KT_SS_SCATTER, KT_SS_HIST, KT_SS_SCAN, KT_SS_SCATTER
 const int PROGRAM[] = {
     KT_FILL_U32,  KT_AREA_CDF, KT_SAMPLE,                                      // sampling
+    KT_ORDER_SMALL, KT_ORDER_COUNT, KT_ORDER_SCAN, KT_ORDER_DEAL, KT_ORDER_BOX,
+    KT_NEAR, KT_NEAR_SHARED,                               // search over ordered clouds
     KT_NORM_MAX,  KT_NORM_MAX, KT_PACK,     KT_SCREEN, KT_SCREEN_ROWS, KT_REFINE,  // screen
     KT_BIDIR8,    KT_BIDIR4,   KT_NN_MERGE, KT_BIDIR_MERGE,  // exact, both directions in one pass
     KT_NN8,       KT_NN4,      KT_NN1,      KT_NN_MERGE,   // exact a -> b (or its heavy rows)
@@ -219,9 +221,20 @@ struct RegionMap {
     size_t in_bytes, out_bytes, total;
 };
 
-size_t scratch_bytes(int T, int V, int F, int Na, int Nb, int precision, bool want_grad) {
+// the search of a request; `ordering` false: without the scratch of ordered clouds, for a budget
+// that holds the request no other way
+Search request_search(int T, int Na, int Nb, int precision, int reduction, bool ordering) {
+    return plan_search(T, Na, Nb, precision, reduction != DC_RED_SIM2REAL_SUM, ordering);
+}
+
+// A request keeps room for any of its precision's searches beside the one it will run, so what
+// admission reserves doesn't depend on that choice unless the ordered clouds need more.
+size_t scratch_bytes(int T, int V, int F, int Na, int Nb, int precision, Search search,
+                     bool want_grad) {
     size_t s = sample_scratch_bytes(T, F);
-    s = std::max(s, chamfer_fwd_scratch_bytes(T, Na, Nb, precision));
+    s = std::max(s, search_scratch_bytes(search, T, Na, Nb));
+    s = std::max(s, search_scratch_bytes(
+                        precision == DC_PREC_BF16_REFINE ? Search::screen : Search::exact, T, Na, Nb));
     if (want_grad) {
         s = std::max(s, chamfer_bwd_scratch_bytes(T, Na, Nb, false));
         s = std::max(s, sample_bwd_scratch_bytes(T, V, F, Na));
@@ -229,7 +242,8 @@ size_t scratch_bytes(int T, int V, int F, int Na, int Nb, int precision, bool wa
     return s;
 }
 
-RegionMap region_map(int T, int V, int F, int Na, int Nb, int precision, bool want_grad) {
+RegionMap region_map(int T, int V, int F, int Na, int Nb, int precision, Search search,
+                     bool want_grad) {
     const size_t TV = (size_t)T * V, TA = (size_t)T * Na, TB = (size_t)T * Nb;
     RegionMap m;
     size_t off = 0;
@@ -256,7 +270,7 @@ RegionMap region_map(int T, int V, int F, int Na, int Nb, int precision, bool wa
     m.ib = take(TB, 4);
     m.gl = want_grad ? take(T, 8) : off;
     m.gpts = want_grad ? take(TA * 3, 4) : off;
-    m.scratch = take(scratch_bytes(T, V, F, Na, Nb, precision, want_grad), 1);
+    m.scratch = take(scratch_bytes(T, V, F, Na, Nb, precision, search, want_grad), 1);
     m.total = off;
     return m;
 }
@@ -298,6 +312,7 @@ struct Req {
     int T = 0, V = 0, F = 0, Na = 0, Nb = 0, precision = 0, reduction = 0;
     uint64_t seed = 0;
     bool want_grad = false, has_w = false;
+    Search search = Search::exact;
     RegionMap map{};
     double pairs = 0;
     int state = Q_QUEUED;
@@ -321,7 +336,8 @@ int issue_request(const Req *r, const Layout &L, unsigned long long *stats) {
     if (rc) return rc;
     // the unidirectional loss needs neither the b -> a search nor its indices
     const bool cols = r->reduction != DC_RED_SIM2REAL_SUM;
-    rc = enqueue_chamfer_fwd(nullptr, L.pts, L.obs, T, Na, Nb, r->precision, r->reduction,
+    rc = enqueue_chamfer_fwd(nullptr, L.pts, L.obs, T, Na, Nb, r->search,
+                             r->precision == DC_PREC_BF16_REFINE, r->reduction,
                              r->has_w ? L.fw : nullptr, L.da, L.ia, cols ? L.db : nullptr,
                              cols ? L.ib : nullptr, L.loss, L.scratch, stats, s);
     if (rc) return rc;
@@ -469,8 +485,11 @@ struct Scheduler {
     size_t host_seg = HOST_SEG_MIN;
 };
 
-size_t request_bytes(int T, int V, int F, int Na, int Nb, int precision, bool want_grad) {
-    return region_map(T, V, F, Na, Nb, precision, want_grad).total;
+size_t request_bytes(int T, int V, int F, int Na, int Nb, int precision, int reduction,
+                     bool want_grad) {
+    return region_map(T, V, F, Na, Nb, precision,
+                      request_search(T, Na, Nb, precision, reduction, true), want_grad)
+        .total;
 }
 
 size_t serving_fixed_bytes() { return sizeof(BatchDesc) * NSLOTS; }
@@ -533,7 +552,7 @@ static int admit(Scheduler *S, Req *r) {
         set_error("device region of a request: allocation failed (forced)");
         return DC_ERR_NOMEM;
     }
-    const size_t n = r->map.total;
+    size_t n = r->map.total;
     if (!S->dpool.carve(n, &r->dev)) {
         int rc = dev_grow(S, n, false);
         if (rc != DC_OK) {
@@ -542,6 +561,15 @@ static int admit(Scheduler *S, Req *r) {
             // for one that holds this request exactly
             dev_release_all(S);
             rc = dev_grow(S, n, true);
+            if (rc == DC_ERR_BUDGET && r->search == Search::ordered) {
+                // beside the direct calls' scratch the budget may still hold the request without
+                // its ordered clouds (the inputs and outputs keep their places in the region)
+                r->search = request_search(r->T, r->Na, r->Nb, r->precision, r->reduction, false);
+                r->map = region_map(r->T, r->V, r->F, r->Na, r->Nb, r->precision, r->search,
+                                    r->want_grad);
+                n = r->map.total;
+                rc = dev_grow(S, n, true);
+            }
             if (rc != DC_OK) return rc;
         }
         if (!S->dpool.carve(n, &r->dev)) {
@@ -786,6 +814,7 @@ static int ensure_scheduler(dc_ctx *ctx) {
     register_sample_kernels(S->kern);
     register_nn_kernels(S->kern);
     register_screen_kernels(S->kern);
+    register_ordered_kernels(S->kern);
     register_sort_kernels(S->kern);
     register_backward_kernels(S->kern);
     register_fill_kernels(S->kern);
@@ -831,8 +860,13 @@ int sched_submit(dc_ctx *ctx, const dc_request *q, dc_result *out, uint64_t *tic
         return DC_ERR_INVALID;
     }
     const bool want_grad = out->grad_verts != nullptr;
-    const RegionMap map =
-        region_map(q->T, q->V, q->F, q->n_sim, q->n_obs, q->precision, want_grad);
+    RegionMap map;
+    Search search;
+    for (int ordering = 1; ordering >= 0; --ordering) {
+        search = request_search(q->T, q->n_sim, q->n_obs, q->precision, q->reduction, ordering != 0);
+        map = region_map(q->T, q->V, q->F, q->n_sim, q->n_obs, q->precision, search, want_grad);
+        if (map.total + serving_fixed_bytes() + CTX_WORDS_BYTES <= ctx->budget) break;
+    }
     if (map.total + serving_fixed_bytes() + CTX_WORDS_BYTES > ctx->budget) {
         set_error("dc_submit: request needs " + std::to_string(map.total) +
                   " bytes, more than the budget holds beside the serving loop's descriptors");
@@ -858,6 +892,7 @@ int sched_submit(dc_ctx *ctx, const dc_request *q, dc_result *out, uint64_t *tic
     r->want_grad = want_grad;
     r->has_w = q->frame_w != nullptr;
     r->map = map;
+    r->search = search;
     r->pairs = (double)q->T * q->n_sim * q->n_obs;
     // the inputs go straight into pinned staging laid out like the region's input prefix
     int rc = host_alloc(S, map.in_bytes, &r->h_in);

@@ -1,8 +1,11 @@
 // Backward passes: the Chamfer gradient through the saved neighbours (Sec. III-A, Eq. 1/2) and
-// the sampling gradient through Eq. 4 (Sec. III-B).  Both are gathers over segments built by the
-// stable atomic-free sort, summed in increasing index order and in double (each output rounded
+// the sampling gradient through Eq. 4 (Sec. III-B).  Both are gathers over segments of equal keys
+// (listed in LDS, or for very many items built by a stable sort), each put into increasing index
+// order first and summed in an order fixed by that, in double (each output rounded
 // once to float), so every result is bitwise reproducible, independent of scheduling, and within a
 // few units of 2^-24 of the sum of its terms' magnitudes however long a segment is.
+#include <algorithm>
+
 #include "batch.h"
 
 namespace dc {
@@ -192,6 +195,399 @@ __global__ __launch_bounds__(BW_THREADS) void k_vertex_grad(VertexGradParams p) 
     vertex_grad_body(p, grid_blk_xcd());
 }
 
+// ---------------------------------------------------------------- sums over small segments
+// The same three sums without a sort in memory, for up to GP_MAX items: a workgroup takes a range of
+// keys (rows, faces or vertices), reads all of the items' keys, lists the items of its own keys in
+// LDS, puts each key's items into increasing order and sums over them.  Every workgroup reads all
+// keys, but as a coalesced stream that its neighbours on the XCD read too; nothing is scattered
+// through memory, and one launch takes the place of seven.  The items are listed by LDS atomics in
+// whatever order, but counting, for each, the smaller items of its segment gives each its place:
+// the sums run in the same order on every run.
+//
+// Workgroups of 512 threads, four to a compute unit, for up to GP_WIDE items a frame, else of 1,024,
+// two to a compute unit: fewer workgroups then read the keys.  The three kernels of a backward, 512
+// against 1,024 threads: 40 frames of 8,192 points 44 / 62 us (165 us with sorts), 17 frames of
+// 30,011 x 5,003 (both gradients) 72 / 91 (198), 100 frames of 65,536 607 / 513 (697).
+constexpr int GP_SMALL = 512, GP_LARGE = 1024;
+constexpr int GP_WIDE = 32768;
+constexpr int GP_IBITS = 17;      // bits of an item in a listed word, below its key
+constexpr int GP_MAX = 1 << GP_IBITS;
+
+// items listed at once, and most keys, of a workgroup of TH threads
+template <int TH>
+constexpr int gp_cap() { return 4 * TH; }
+static_assert(gp_cap<GP_LARGE>() <= 1 << (32 - GP_IBITS), "a key and an item share a word");
+
+template <int TH>
+struct GroupLds {
+    int start[gp_cap<TH>() + 4];    // first position of each key's items, over the workgroup's range
+    int cursor[gp_cap<TH>()];
+    unsigned listed[gp_cap<TH>()];
+    int item[gp_cap<TH>()];         // the items, by key and then in increasing order
+    int wsum[TH / 64];
+    double part[TH / 64][9];
+};
+
+// a sum of M components by the G lanes of a key's team (in every lane), in a fixed order
+template <int M>
+__device__ __forceinline__ void team_sum(double (&v)[M], int G) {
+    for (int off = 1; off < G; off <<= 1)
+#pragma unroll
+        for (int k = 0; k < M; ++k) v[k] += __shfl_xor(v[k], off, 64);
+}
+
+// visit(i, keys[i]) for every i, by the workgroup: four keys a load (keys are 4-byte aligned, which
+// is all a 16-byte load needs), four loads of a thread in flight
+struct __attribute__((packed, aligned(4))) Keys4 {
+    int32_t k[4];
+};
+
+template <int TH, class Visit>
+__device__ __forceinline__ void each_key(const int32_t *__restrict__ keys, int n, const Visit &visit) {
+    constexpr int U = 4;
+    const int whole = n & ~3;
+    for (int i0 = 4 * (int)threadIdx.x; i0 < whole; i0 += 4 * U * TH) {
+        Keys4 w[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            w[u] = *reinterpret_cast<const Keys4 *>(keys + min(i0 + 4 * u * TH, whole - 4));
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int i = i0 + 4 * u * TH;
+            if (i < whole)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) visit(i + e, w[u].k[e]);
+        }
+    }
+    if ((int)threadIdx.x < n - whole) visit(whole + (int)threadIdx.x, keys[whole + threadIdx.x]);
+}
+
+// For every key in [k0, k0 + nk): `own(key)` reads what the key itself needs, `each(own, item, on, sum)`
+// adds an item to its sum (nothing unless `on`), `put(key, own, sum)` takes the total; a thread has U
+// keys in hand at a time and G lanes share one.  A round lists as many keys as fit CAP items; a key
+// with more is summed by the whole workgroup, straight from the keys, each thread its every
+// TH-th item.
+template <int TH, int M, int U, class Own, class Each, class Put>
+__device__ __forceinline__ void grouped_sums(const int32_t *__restrict__ keys, int n, int k0, int nk,
+                                             int G, GroupLds<TH> &s, const Own &own, const Each &each,
+                                             const Put &put) {
+    constexpr int CAP = gp_cap<TH>(), WAVES = TH / 64;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    for (int k = tid; k < nk; k += TH) s.cursor[k] = 0;
+    __syncthreads();
+    each_key<TH>(keys, n, [&](int i, int key) {
+        const int k = key - k0;
+        if ((unsigned)k < (unsigned)nk) atomicAdd(&s.cursor[k], 1);
+    });
+    __syncthreads();
+    {  // counts to starts
+        constexpr int PER = CAP / TH;
+        int c[PER], sum = 0;
+#pragma unroll
+        for (int u = 0; u < PER; ++u) {
+            const int k = tid * PER + u;
+            c[u] = k < nk ? s.cursor[k] : 0;
+            sum += c[u];
+        }
+        int incl = sum;
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            const int o = __shfl_up(incl, off, 64);
+            if (lane >= off) incl += o;
+        }
+        if (lane == 63) s.wsum[wave] = incl;
+        __syncthreads();
+        int at = incl - sum;
+        for (int w = 0; w < wave; ++w) at += s.wsum[w];
+#pragma unroll
+        for (int u = 0; u < PER; ++u) {
+            const int k = tid * PER + u;
+            if (k <= nk) s.start[k] = at;
+            at += c[u];
+        }
+        if (tid == TH - 1 && nk == CAP) s.start[nk] = at;
+        __syncthreads();
+    }
+    for (int kb = 0; kb < nk;) {
+        const int base = s.start[kb];
+        int ke = nk;  // the keys of the round: the last one whose items still fit
+        if (s.start[nk] - base > CAP) {
+            int lo = kb, hi = nk;
+            while (lo < hi) {
+                const int mid = (lo + hi + 1) >> 1;
+                if (s.start[mid] - base <= CAP)
+                    lo = mid;
+                else
+                    hi = mid - 1;
+            }
+            ke = lo;
+        }
+        // a key with more items than fit: by all threads, each its every 1,024th item
+        const bool giant = ke == kb;
+        if (giant) ke = kb + 1;
+        const int total = s.start[ke] - base;
+        if (total > 0 && !giant) {
+            for (int k = kb + tid; k < ke; k += TH) s.cursor[k] = s.start[k] - base;
+            __syncthreads();
+            each_key<TH>(keys, n, [&](int i, int key) {
+                const int k = key - k0;
+                if (k >= kb && k < ke)
+                    s.listed[atomicAdd(&s.cursor[k], 1)] = ((unsigned)k << GP_IBITS) | (unsigned)i;
+            });
+            __syncthreads();
+            for (int p = tid; p < total; p += TH) {
+                const unsigned w = s.listed[p];
+                const int k = (int)(w >> GP_IBITS);
+                const int lo = s.start[k] - base, hi = s.start[k + 1] - base;
+                int at = lo;
+#pragma unroll 4
+                for (int e = lo; e < hi; ++e) at += s.listed[e] < w ? 1 : 0;
+                s.item[at] = (int)(w & (GP_MAX - 1));
+            }
+            __syncthreads();
+        }
+        if (giant) {
+            const auto whole = own(k0 + kb);
+            double v[M];
+#pragma unroll
+            for (int m = 0; m < M; ++m) v[m] = 0.0;
+#pragma unroll 1
+            for (int i = tid; i < n; i += TH) each(whole, i, keys[i] == k0 + kb, v);
+            team_sum(v, 64);
+            if (lane == 0)
+#pragma unroll
+                for (int m = 0; m < M; ++m) s.part[wave][m] = v[m];
+            __syncthreads();
+        }
+        const int per = TH / G, l = tid & (G - 1);
+#pragma unroll 1
+        for (int k = giant ? kb + tid : kb + tid / G; k < ke; k += U * per) {
+            int ku[U], e[U], hi[U];
+            double v[U][M];
+            decltype(own(0)) mine[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const bool ok = k + u * per < ke;
+                ku[u] = ok ? k + u * per : k;
+                mine[u] = own(k0 + ku[u]);
+                e[u] = s.start[ku[u]] - base + l;
+                hi[u] = ok && !giant ? s.start[ku[u] + 1] - base : 0;
+#pragma unroll
+                for (int m = 0; m < M; ++m) v[u][m] = 0.0;
+            }
+#pragma unroll 1
+            for (;;) {  // an item of each of the U keys at a time, their loads in flight together
+                bool more = false;
+#pragma unroll
+                for (int u = 0; u < U; ++u) more = more || e[u] < hi[u];
+                if (!more) break;
+                int i[U];
+#pragma unroll
+                for (int u = 0; u < U; ++u) i[u] = s.item[e[u] < hi[u] ? e[u] : 0];
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    each(mine[u], i[u], e[u] < hi[u], v[u]);
+                    e[u] += G;
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                team_sum(v[u], G);
+                if (giant)
+#pragma unroll 1
+                    for (int w = 0; w < WAVES; ++w)
+#pragma unroll
+                        for (int m = 0; m < M; ++m) v[u][m] += s.part[w][m];
+                if (l == 0 && k + u * per < ke) put(k0 + ku[u], mine[u], v[u]);
+            }
+        }
+        __syncthreads();  // the next round lists anew
+        kb = ke;
+    }
+}
+
+// keys per workgroup, workgroups, and lanes per key for `n` items of `K` keys, `sets` times over
+struct GroupPlan {
+    int threads, keys, ranges, team;
+};
+
+// x = range of rows, y = frame, z = side - first (side 0: the gradient to a, 1: to b)
+struct GroupChamferParams {
+    const double *grad_loss;
+    const float *frame_w;
+    struct Side {
+        const float *X;
+        const int32_t *nn;  // x's neighbours in y, or NULL
+        float *gX;
+        int N, keys, team, pad;
+    } side[2];
+    double cself[2];  // cs of the two sides; cm of one is cs of the other
+    int first, pad;   // the side of z = 0
+};
+
+template <int TH>
+__device__ __forceinline__ void group_chamfer_body(const GroupChamferParams &pr, const Blk &blk) {
+    __shared__ GroupLds<TH> lds;
+    const bool b = blk.z + pr.first != 0;
+    const GroupChamferParams::Side x = b ? pr.side[1] : pr.side[0], y = b ? pr.side[0] : pr.side[1];
+    const int t = blk.y, k0 = blk.x * x.keys;
+    if (k0 >= x.N) return;
+    const int nk = min(x.keys, x.N - k0);
+    const double g = pr.grad_loss[t] * (pr.frame_w ? (double)pr.frame_w[t] : 1.0);
+    const double cs = (b ? pr.cself[1] : pr.cself[0]) * g, cm = (b ? pr.cself[0] : pr.cself[1]) * g;
+    const float *xt = x.X + (size_t)t * x.N * 3;
+    const float *yt = y.X + (size_t)t * y.N * 3;
+    struct Own {
+        float x[3], y[3];  // the row, and its neighbour
+        bool near;
+    };
+    auto own = [&](int i) {
+        Own o;
+        const int j = cs != 0.0 ? x.nn[(size_t)t * x.N + i] : -1;
+        o.near = (unsigned)j < (unsigned)y.N;  // indices outside [0, Ny) contribute nothing
+        const float *py = yt + 3 * (size_t)(o.near ? j : 0);
+#pragma unroll
+        for (int d = 0; d < 3; ++d) {
+            o.x[d] = xt[3 * (size_t)i + d];
+            o.y[d] = py[d];
+        }
+        return o;
+    };
+    // in double (each difference of two floats is exact there) and rounded once to float, as below
+    auto each = [&](const Own &o, int j, bool on, double (&v)[3]) {
+        const float *py = yt + 3 * (size_t)j;
+        const float d0 = py[0], d1 = py[1], d2 = py[2];
+        v[0] += on ? (double)o.x[0] - (double)d0 : 0.0;
+        v[1] += on ? (double)o.x[1] - (double)d1 : 0.0;
+        v[2] += on ? (double)o.x[2] - (double)d2 : 0.0;
+    };
+    auto put = [&](int i, const Own &o, double (&v)[3]) {
+        float *g3 = x.gX + ((size_t)t * x.N + i) * 3;
+        float r[3];
+#pragma unroll
+        for (int d = 0; d < 3; ++d) {
+            double s = 0.0;
+            if (o.near) s = cs * ((double)o.x[d] - (double)o.y[d]);
+            if (cm != 0.0) s += cm * v[d];
+            r[d] = (float)s;
+        }
+        g3[0] = r[0];
+        g3[1] = r[1];
+        g3[2] = r[2];
+    };
+    // without the mutual term there is nothing to group
+    grouped_sums<TH, 3, 2>(y.nn ? y.nn + (size_t)t * y.N : nullptr, cm != 0.0 ? y.N : 0, k0, nk, x.team,
+                       lds, own, each, put);
+}
+
+template <int TH>
+__global__ __launch_bounds__(TH, 8) void k_group_chamfer(GroupChamferParams p) {
+    group_chamfer_body<TH>(p, grid_blk_xcd());
+}
+
+// x = range of faces, y = frame
+struct GroupFaceParams {
+    const float *gpts;
+    const float *bary;
+    const int32_t *face_idx;
+    float *fg;
+    int F, N, keys, team;
+};
+
+template <int TH>
+__device__ __forceinline__ void group_face_body(const GroupFaceParams &pr, const Blk &blk) {
+    __shared__ GroupLds<TH> lds;
+    const int t = blk.y, k0 = blk.x * pr.keys;
+    const float *gt = pr.gpts + (size_t)t * pr.N * 3;
+    const float *bt = pr.bary + (size_t)t * pr.N * 3;
+    float *ft = pr.fg + (size_t)t * pr.F * 9;
+    auto own = [](int) { return 0; };
+    auto each = [&](int, int i, bool on, double (&v)[9]) {
+        const float *g = gt + 3 * (size_t)i, *b = bt + 3 * (size_t)i;
+        const float f0 = g[0], f1 = g[1], f2 = g[2], w3[3] = {b[0], b[1], b[2]};
+        const double g0 = on ? f0 : 0.f, g1 = on ? f1 : 0.f, g2 = on ? f2 : 0.f;
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            const double w = on ? w3[c] : 0.f;
+            v[3 * c] = __builtin_fma(w, g0, v[3 * c]);
+            v[3 * c + 1] = __builtin_fma(w, g1, v[3 * c + 1]);
+            v[3 * c + 2] = __builtin_fma(w, g2, v[3 * c + 2]);
+        }
+    };
+    auto put = [&](int f, int, double (&v)[9]) {
+#pragma unroll
+        for (int m = 0; m < 9; ++m) ft[9 * (size_t)f + m] = (float)v[m];
+    };
+    grouped_sums<TH, 9, 1>(pr.face_idx + (size_t)t * pr.N, pr.N, k0, min(pr.keys, pr.F - k0), pr.team, lds,
+                       own, each, put);
+}
+
+template <int TH>
+__global__ __launch_bounds__(TH, 8) void k_group_face(GroupFaceParams p) {
+    group_face_body<TH>(p, grid_blk_xcd());
+}
+
+// x = range of vertices, y = frame
+struct GroupVertexParams {
+    const float *fg;
+    const int32_t *faces;
+    float *gverts;
+    int V, F, keys, team;
+};
+
+template <int TH>
+__device__ __forceinline__ void group_vertex_body(const GroupVertexParams &pr, const Blk &blk) {
+    __shared__ GroupLds<TH> lds;
+    const int t = blk.y, k0 = blk.x * pr.keys;
+    const float *ft = pr.fg + (size_t)t * pr.F * 9;
+    float *gv = pr.gverts + (size_t)t * pr.V * 3;
+    auto own = [](int) { return 0; };
+    auto each = [&](int, int fc, bool on, double (&v)[3]) {  // fc = 3 f + c
+        const float *p = ft + 3 * (size_t)fc;
+        const float p0 = p[0], p1 = p[1], p2 = p[2];
+        v[0] += on ? (double)p0 : 0.0;
+        v[1] += on ? (double)p1 : 0.0;
+        v[2] += on ? (double)p2 : 0.0;
+    };
+    auto put = [&](int v, int, double (&s)[3]) {
+#pragma unroll
+        for (int d = 0; d < 3; ++d) gv[3 * (size_t)v + d] = (float)s[d];
+    };
+    grouped_sums<TH, 3, 2>(pr.faces, 3 * pr.F, k0, min(pr.keys, pr.V - k0), pr.team, lds, own, each, put);
+}
+
+template <int TH>
+__global__ __launch_bounds__(TH, 8) void k_group_vertex(GroupVertexParams p) {
+    group_vertex_body<TH>(p, grid_blk_xcd());
+}
+
+// keys per workgroup, so that its items are about 3/4 of what fits at once and there are workgroups
+// for the chip; lanes per key, by the items an average key has
+GroupPlan group_plan(long n, long K, long sets) {
+    GroupPlan g;
+    g.threads = n > GP_WIDE ? GP_LARGE : GP_SMALL;
+    const long cap = 4L * g.threads;
+    const long spread = (K * sets + 511) / 512;  // 512 workgroups
+    const long keys = std::min({K * (cap * 3 / 4) / std::max(n, 1L), std::max(spread, 16L), cap, K});
+    g.keys = (int)std::max(keys, 1L);
+    g.ranges = (int)((K + g.keys - 1) / g.keys);
+    const long avg = n / std::max(K, 1L);
+    g.team = avg < 2 ? 1 : (avg < 16 ? 4 : (avg < 128 ? 16 : 64));
+    return g;
+}
+
+// Up to GP_MAX items: beyond, so many workgroups would read all keys that the sort is the cheaper way.
+bool grouped_pays(long n) { return n <= GP_MAX; }
+
+template <class P>
+void dispatch_group(int type, void (*small)(P), void (*large)(P), int threads, dim3 grid, const P &p,
+                    hipStream_t s) {
+    if (threads == GP_LARGE)
+        dispatch(type + 1, large, grid, GP_LARGE, p, s);
+    else
+        dispatch(type, small, grid, GP_SMALL, p, s);
+}
+
 }  // namespace
 
 size_t chamfer_bwd_scratch_bytes(int T, int Na, int Nb, bool want_b) {
@@ -201,6 +597,29 @@ size_t chamfer_bwd_scratch_bytes(int T, int Na, int Nb, bool want_b) {
         s += 2 * Arena::need((size_t)T * Na, 4) + segsort_scratch_bytes(T, Na) +
              Arena::need((size_t)T * (Nb + 1), 4);
     return s;
+}
+
+// one side by the sort: x's mutual terms are the y's grouped by their neighbour in x
+static void launch_sorted_side(ChamferBwdParams &cp, const int32_t *nn_y, int T, Arena &ar,
+                               hipStream_t s) {
+    int32_t *k = ar.take<int32_t>((size_t)T * cp.Ny);
+    int32_t *v = ar.take<int32_t>((size_t)T * cp.Ny);
+    char *ss = ar.take<char>(segsort_scratch_bytes(T, cp.Ny));
+    int32_t *st = ar.take<int32_t>((size_t)T * (cp.Nx + 1));
+    cp.ystart = st;
+    cp.yvals_sorted = v;
+    if (cp.cmutual != 0.0) {
+        // valid neighbours lie in [0, Nx): Nx - 1 is the key limit, out-of-range ones are marked
+        launch_segsort(nn_y, T, cp.Ny, cp.Nx - 1, k, v, ss, s, true);
+        BoundsParams bp;
+        bp.sorted = k;
+        bp.start = st;
+        bp.N = cp.Ny;
+        bp.K = cp.Nx;
+        dispatch(KT_BOUNDS, k_bounds, dim3((cp.Ny + BW_THREADS) / BW_THREADS, T), BW_THREADS, bp, s);
+    }
+    dispatch(KT_CHAMFER_BWD, k_chamfer_bwd, dim3((cp.Nx + BW_THREADS - 1) / BW_THREADS, T),
+             BW_THREADS, cp, s);
 }
 
 void launch_chamfer_bwd(const double *grad_loss, const float *a, const float *b,
@@ -213,63 +632,51 @@ void launch_chamfer_bwd(const double *grad_loss, const float *a, const float *b,
     Arena ar;
     ar.base = scratch;
     ar.cap = chamfer_bwd_scratch_bytes(T, Na, Nb, grad_b != nullptr);
-    // segments of b grouped by their neighbour in a (needed when beta != 0)
-    int32_t *kb = ar.take<int32_t>((size_t)T * Nb);
-    int32_t *vb = ar.take<int32_t>((size_t)T * Nb);
-    char *ssb = ar.take<char>(segsort_scratch_bytes(T, Nb));
-    int32_t *sb = ar.take<int32_t>((size_t)T * (Na + 1));
-    if (beta != 0.0) {
-        // valid neighbours lie in [0, Na): Na - 1 is the key limit, out-of-range ones are marked
-        launch_segsort(idx_b, T, Nb, Na - 1, kb, vb, ssb, s, true);
-        BoundsParams bp;
-        bp.sorted = kb;
-        bp.start = sb;
-        bp.N = Nb;
-        bp.K = Na;
-        dispatch(KT_BOUNDS, k_bounds, dim3((Nb + BW_THREADS) / BW_THREADS, T), BW_THREADS, bp, s);
+    // the a side groups the b points (when beta != 0), the b side the a points
+    const long items_a = beta != 0.0 ? Nb : 0;
+    const bool group_a = grouped_pays(items_a), group_b = grad_b && grouped_pays(Na);
+    if (group_a || group_b) {
+        GroupChamferParams gp;
+        gp.grad_loss = grad_loss;
+        gp.frame_w = frame_w;
+        const GroupPlan pa = group_plan(items_a, Na, T), pb = group_plan(Na, Nb, T);
+        gp.side[0] = {a, idx_a, grad_a, Na, pa.keys, pa.team, 0};
+        gp.side[1] = {b, beta != 0.0 ? idx_b : nullptr, grad_b, Nb, pb.keys, pb.team, 0};
+        gp.cself[0] = 2.0 * alpha;
+        gp.cself[1] = 2.0 * beta;
+        gp.first = group_a ? 0 : 1;
+        gp.pad = 0;
+        // one launch for both sides; a small workgroup's range also fits a large one
+        const int threads = std::max(group_a ? pa.threads : 0, group_b ? pb.threads : 0);
+        dispatch_group(KT_GROUP_CHAMFER, k_group_chamfer<GP_SMALL>, k_group_chamfer<GP_LARGE>, threads,
+                       dim3(std::max(group_a ? pa.ranges : 0, group_b ? pb.ranges : 0), T,
+                            group_a && group_b ? 2 : 1),
+                       gp, s);
     }
     ChamferBwdParams cp;
     cp.grad_loss = grad_loss;
-    cp.X = a;
-    cp.Y = b;
-    cp.nn_x = idx_a;
-    cp.ystart = sb;
-    cp.yvals_sorted = vb;
     cp.frame_w = frame_w;
-    cp.gX = grad_a;
-    cp.cself = 2.0 * alpha;
-    cp.cmutual = 2.0 * beta;
-    cp.Nx = Na;
-    cp.Ny = Nb;
-    dispatch(KT_CHAMFER_BWD, k_chamfer_bwd, dim3((Na + BW_THREADS - 1) / BW_THREADS, T),
-             BW_THREADS, cp, s);
-    if (grad_b) {
-        int32_t *ka = ar.take<int32_t>((size_t)T * Na);
-        int32_t *va = ar.take<int32_t>((size_t)T * Na);
-        char *ssa = ar.take<char>(segsort_scratch_bytes(T, Na));
-        int32_t *sa = ar.take<int32_t>((size_t)T * (Nb + 1));
-        launch_segsort(idx_a, T, Na, Nb - 1, ka, va, ssa, s, true);
-        BoundsParams bq;
-        bq.sorted = ka;
-        bq.start = sa;
-        bq.N = Na;
-        bq.K = Nb;
-        dispatch(KT_BOUNDS, k_bounds, dim3((Na + BW_THREADS) / BW_THREADS, T), BW_THREADS, bq, s);
-        ChamferBwdParams cq;
-        cq.grad_loss = grad_loss;
-        cq.X = b;
-        cq.Y = a;
-        cq.nn_x = idx_b;
-        cq.ystart = sa;
-        cq.yvals_sorted = va;
-        cq.frame_w = frame_w;
-        cq.gX = grad_b;
-        cq.cself = 2.0 * beta;
-        cq.cmutual = 2.0 * alpha;
-        cq.Nx = Nb;
-        cq.Ny = Na;
-        dispatch(KT_CHAMFER_BWD, k_chamfer_bwd, dim3((Nb + BW_THREADS - 1) / BW_THREADS, T),
-                 BW_THREADS, cq, s);
+    if (!group_a) {
+        cp.X = a;
+        cp.Y = b;
+        cp.nn_x = idx_a;
+        cp.gX = grad_a;
+        cp.cself = 2.0 * alpha;
+        cp.cmutual = 2.0 * beta;
+        cp.Nx = Na;
+        cp.Ny = Nb;
+        launch_sorted_side(cp, idx_b, T, ar, s);
+    }
+    if (grad_b && !group_b) {
+        cp.X = b;
+        cp.Y = a;
+        cp.nn_x = idx_b;
+        cp.gX = grad_b;
+        cp.cself = 2.0 * beta;
+        cp.cmutual = 2.0 * alpha;
+        cp.Nx = Nb;
+        cp.Ny = Na;
+        launch_sorted_side(cp, idx_a, T, ar, s);
     }
 }
 
@@ -286,40 +693,70 @@ void launch_sample_bwd(const float *grad_points, const int32_t *faces, const int
     Arena ar;
     ar.base = scratch;
     ar.cap = sample_bwd_scratch_bytes(T, V, F, N);
-    int32_t *fk = ar.take<int32_t>((size_t)T * N);
-    int32_t *fv = ar.take<int32_t>((size_t)T * N);
-    char *ss1 = ar.take<char>(segsort_scratch_bytes(T, N));
-    int32_t *fstart = ar.take<int32_t>((size_t)T * (F + 1));
+    float *fg = ar.take<float>((size_t)T * F * 9);
+    BoundsParams bp;
+    // points grouped by face (face -1 of a degenerate frame is left out: it belongs to no face)
+    if (grouped_pays(N)) {
+        const GroupPlan pf = group_plan(N, F, T);
+        GroupFaceParams gf;
+        gf.gpts = grad_points;
+        gf.bary = bary;
+        gf.face_idx = face_idx;
+        gf.fg = fg;
+        gf.F = F;
+        gf.N = N;
+        gf.keys = pf.keys;
+        gf.team = pf.team;
+        dispatch_group(KT_GROUP_FACE, k_group_face<GP_SMALL>, k_group_face<GP_LARGE>, pf.threads,
+                       dim3(pf.ranges, T), gf, s);
+    } else {
+        int32_t *fk = ar.take<int32_t>((size_t)T * N);
+        int32_t *fv = ar.take<int32_t>((size_t)T * N);
+        char *ss1 = ar.take<char>(segsort_scratch_bytes(T, N));
+        int32_t *fstart = ar.take<int32_t>((size_t)T * (F + 1));
+        // (face -1 sorts last, as key F, and is unused)
+        launch_segsort(face_idx, T, N, F, fk, fv, ss1, s);
+        bp.sorted = fk;
+        bp.start = fstart;
+        bp.N = N;
+        bp.K = F;
+        dispatch(KT_BOUNDS, k_bounds, dim3((N + BW_THREADS) / BW_THREADS, T), BW_THREADS, bp, s);
+        FaceGradParams fp;
+        fp.gpts = grad_points;
+        fp.bary = bary;
+        fp.pts_by_face = fv;
+        fp.face_start = fstart;
+        fp.fg = fg;
+        fp.F = F;
+        fp.N = N;
+        dispatch(KT_FACE_GRAD, k_face_grad, dim3((F + BW_THREADS - 1) / BW_THREADS, T), BW_THREADS,
+                 fp, s);
+    }
+    // (face, corner) slots grouped by vertex: the vertex-incidence lists of the topology
+    if (grouped_pays(3L * F)) {
+        const GroupPlan pv = group_plan(3L * F, V, T);
+        GroupVertexParams gv;
+        gv.fg = fg;
+        gv.faces = faces;
+        gv.gverts = grad_verts;
+        gv.V = V;
+        gv.F = F;
+        gv.keys = pv.keys;
+        gv.team = pv.team;
+        dispatch_group(KT_GROUP_VERTEX, k_group_vertex<GP_SMALL>, k_group_vertex<GP_LARGE>, pv.threads,
+                       dim3(pv.ranges, T), gv, s);
+        return;
+    }
     int32_t *ck = ar.take<int32_t>((size_t)3 * F);
     int32_t *cv = ar.take<int32_t>((size_t)3 * F);
     char *ss2 = ar.take<char>(segsort_scratch_bytes(1, 3 * F));
     int32_t *vstart = ar.take<int32_t>((size_t)V + 1);
-    float *fg = ar.take<float>((size_t)T * F * 9);
-    // points grouped by face (face -1 of a degenerate frame sorts last, as key F, and is unused)
-    launch_segsort(face_idx, T, N, F, fk, fv, ss1, s);
-    BoundsParams bp;
-    bp.sorted = fk;
-    bp.start = fstart;
-    bp.N = N;
-    bp.K = F;
-    dispatch(KT_BOUNDS, k_bounds, dim3((N + BW_THREADS) / BW_THREADS, T), BW_THREADS, bp, s);
-    // (face, corner) slots grouped by vertex: the vertex-incidence CSR of the topology
     launch_segsort(faces, 1, 3 * F, V, ck, cv, ss2, s);
     bp.sorted = ck;
     bp.start = vstart;
     bp.N = 3 * F;
     bp.K = V;
     dispatch(KT_BOUNDS, k_bounds, dim3((3 * F + BW_THREADS) / BW_THREADS, 1), BW_THREADS, bp, s);
-    FaceGradParams fp;
-    fp.gpts = grad_points;
-    fp.bary = bary;
-    fp.pts_by_face = fv;
-    fp.face_start = fstart;
-    fp.fg = fg;
-    fp.F = F;
-    fp.N = N;
-    dispatch(KT_FACE_GRAD, k_face_grad, dim3((F + BW_THREADS - 1) / BW_THREADS, T), BW_THREADS, fp,
-             s);
     VertexGradParams vp;
     vp.fg = fg;
     vp.corners_by_vertex = cv;
@@ -335,6 +772,13 @@ void register_backward_kernels(BatchedKernel *table) {
     table[KT_CHAMFER_BWD] = batched_kernel<ChamferBwdParams, chamfer_bwd_body, BW_THREADS, 1024>();
     table[KT_BOUNDS] = batched_kernel<BoundsParams, bounds_body, BW_THREADS, 512>();
     table[KT_FACE_GRAD] = batched_kernel<FaceGradParams, face_grad_body, BW_THREADS, 1024>();
+    // each type's large workgroups follow its small ones
+    table[KT_GROUP_CHAMFER] = batched_kernel<GroupChamferParams, group_chamfer_body<GP_SMALL>, GP_SMALL, 1024, 8>();
+    table[KT_GROUP_CHAMFER + 1] = batched_kernel<GroupChamferParams, group_chamfer_body<GP_LARGE>, GP_LARGE, 512, 8>();
+    table[KT_GROUP_FACE] = batched_kernel<GroupFaceParams, group_face_body<GP_SMALL>, GP_SMALL, 1024, 8>();
+    table[KT_GROUP_FACE + 1] = batched_kernel<GroupFaceParams, group_face_body<GP_LARGE>, GP_LARGE, 512, 8>();
+    table[KT_GROUP_VERTEX] = batched_kernel<GroupVertexParams, group_vertex_body<GP_SMALL>, GP_SMALL, 1024, 8>();
+    table[KT_GROUP_VERTEX + 1] = batched_kernel<GroupVertexParams, group_vertex_body<GP_LARGE>, GP_LARGE, 512, 8>();
     table[KT_VERTEX_GRAD] = batched_kernel<VertexGradParams, vertex_grad_body, BW_THREADS, 1024>();
 }
 

@@ -82,10 +82,13 @@ enum KernelType : int {
     KT_BOUNDS,
     KT_FACE_GRAD,
     KT_VERTEX_GRAD,
+    KT_GROUP_CHAMFER,        // (small workgroups, large ones)
+    KT_GROUP_FACE = KT_GROUP_CHAMFER + 2,
+    KT_GROUP_VERTEX = KT_GROUP_FACE + 2,
+    KT_AFTER_GROUP = KT_GROUP_VERTEX + 1,
     KT_BIDIR8,
     KT_BIDIR4,
     KT_BIDIR_MERGE,
-    KT_SS_SMALL,
     KT_ORDER_SMALL,
     KT_ORDER_COUNT,
     KT_ORDER_SCAN,
@@ -105,7 +108,7 @@ struct OpRec {
     alignas(16) unsigned char p[OP_PARAM_BYTES];
 };
 
-constexpr int MAX_STAGES = 80;   // length of the serving program
+constexpr int MAX_STAGES = 84;   // length of the serving program
 constexpr int MAX_BATCH = 32;    // requests per batch
 constexpr int MAX_OPS = 72 * MAX_BATCH - 1;
 

@@ -101,10 +101,10 @@ void fill_f64(double *p, int n, double v, hipStream_t s) {
 }
 
 // The serving program: every request's recorded launches form a subsequence of it.  Exact
-// searches may use any of the three queries-per-lane variants; each sort is either the one-launch
-// sort of small segments or up to four 8-bit digit passes (keys below 2^32).
+// searches may use any of the three queries-per-lane variants; each sort is up to four 8-bit digit
+// passes (keys below 2^32).
 #define SORT_PASSES                                                                          \
-    KT_SS_SMALL, KT_SS_HIST, KT_SS_SCAN, KT_SS_SCATTER, KT_SS_HIST, KT_SS_SCAN, KT_SS_SCATTER, \
+    KT_SS_HIST, KT_SS_SCAN, KT_SS_SCATTER, KT_SS_HIST, KT_SS_SCAN, KT_SS_SCATTER, \
         KT_SS_HIST, KT_SS_SCAN, KT_SS_SCATTER, KT_SS_HIST, KT_SS_SCAN, KT_SS_SCATTER
 const int PROGRAM[] = {
     KT_FILL_U32,  KT_AREA_CDF, KT_SAMPLE,                                      // sampling
@@ -115,8 +115,10 @@ const int PROGRAM[] = {
     KT_NN8,       KT_NN4,      KT_NN1,      KT_NN_MERGE,   // exact a -> b (or its heavy rows)
     KT_COLMERGE,  KT_COLREFINE,                            // screen, columns
     KT_NN8,       KT_NN4,      KT_NN1,      KT_NN_MERGE,   // exact b -> a (or its heavy columns)
-    KT_LOSS,      KT_FILL_F64, SORT_PASSES, KT_BOUNDS, KT_CHAMFER_BWD,         // Chamfer bwd
-    SORT_PASSES,  KT_BOUNDS,   SORT_PASSES, KT_BOUNDS,  KT_FACE_GRAD, KT_VERTEX_GRAD};
+    KT_LOSS,      KT_FILL_F64,
+    KT_GROUP_CHAMFER, KT_GROUP_CHAMFER + 1, SORT_PASSES, KT_BOUNDS, KT_CHAMFER_BWD,  // Chamfer bwd
+    KT_GROUP_FACE, KT_GROUP_FACE + 1, SORT_PASSES, KT_BOUNDS, KT_FACE_GRAD,          // sampling bwd
+    KT_GROUP_VERTEX, KT_GROUP_VERTEX + 1, SORT_PASSES, KT_BOUNDS, KT_VERTEX_GRAD};
 #undef SORT_PASSES
 constexpr int NPROG = (int)(sizeof(PROGRAM) / sizeof(PROGRAM[0]));
 static_assert(NPROG <= MAX_STAGES, "program longer than the descriptor");

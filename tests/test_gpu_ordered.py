@@ -118,7 +118,6 @@ def test_not_finite(T, n):
     def exhaustive(Q, P):
         with np.errstate(all="ignore"):
             best = np.full(len(Q), np.inf, np.float32)
-            idx = np.zeros(len(Q), np.int32)
             for i in range(0, len(Q), 200):
                 d = Q[i:i + 200, None] - P[None]  # float32 throughout; fma in double, rounded once
                 s = (d[..., 0] * d[..., 0]).astype(np.float64)
@@ -128,22 +127,22 @@ def test_not_finite(T, n):
                 s = s.astype(np.float32)
                 s[np.isnan(s)] = np.inf
                 best[i:i + 200] = s.min(1)
-                idx[i:i + 200] = s.argmin(1)
-        return best, idx
+        return best
 
     for t in (0, T - 1, T // 2):
         for Q, P, side in ((A, B, "a"), (B, A, "b")):
-            best, idx = exhaustive(Q[t], P[t])
+            some = slice(t % 3, None, 3 if n < 5000 else 25)
+            Qs, got, gd = Q[t][some], g["idx_" + side][t][some], g["dist_" + side][t][some]
+            best = exhaustive(Qs, P[t])
             fin = np.isfinite(best)
-            assert np.array_equal(np.isfinite(g["dist_" + side][t]), fin), (t, side)
-            assert np.allclose(g["dist_" + side][t][fin], best[fin], rtol=1e-6, atol=0)
-            got = g["idx_" + side][t]
+            assert np.array_equal(np.isfinite(gd), fin), (t, side)
+            assert np.allclose(gd[fin], best[fin], rtol=1e-6, atol=0)
             assert got.min() >= 0 and got.max() < n
             with np.errstate(all="ignore"):
-                dg = Q[t].astype(np.float64) - P[t][got].astype(np.float64)
+                dg = Qs.astype(np.float64) - P[t][got].astype(np.float64)
                 assert np.allclose((dg[fin] ** 2).sum(1), best[fin], rtol=1e-6, atol=0)
                 for q in np.nonzero(~fin)[0][:200]:
-                    d = Q[t][q][None] - P[t][:64]
+                    d = Qs[q][None] - P[t][:64]
                     s = (d * d).sum(1)
                     inf = np.nonzero(np.isposinf(s))[0]
                     assert got[q] == (inf[0] if len(inf) else 0), (t, side, q)

@@ -63,6 +63,7 @@ enum KernelType : int {
     KT_FILL_F64,
     KT_AREA_CDF,
     KT_SAMPLE,
+    KT_SAMPLE_WIDE,
     KT_NORM_MAX,
     KT_PACK,
     KT_SCREEN,

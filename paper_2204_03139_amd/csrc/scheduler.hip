@@ -107,7 +107,7 @@ void fill_f64(double *p, int n, double v, hipStream_t s) {
     KT_SS_HIST, KT_SS_SCAN, KT_SS_SCATTER, KT_SS_HIST, KT_SS_SCAN, KT_SS_SCATTER, \
         KT_SS_HIST, KT_SS_SCAN, KT_SS_SCATTER, KT_SS_HIST, KT_SS_SCAN, KT_SS_SCATTER
 const int PROGRAM[] = {
-    KT_FILL_U32,  KT_AREA_CDF, KT_SAMPLE,                                      // sampling
+    KT_FILL_U32,  KT_AREA_CDF, KT_SAMPLE,   KT_SAMPLE_WIDE,                    // sampling
     KT_ORDER_SMALL, KT_ORDER_COUNT, KT_ORDER_SCAN, KT_ORDER_DEAL, KT_ORDER_BOX,
     KT_NEAR, KT_NEAR_SHARED,                               // search over ordered clouds
     KT_NORM_MAX,  KT_NORM_MAX, KT_PACK,     KT_SCREEN, KT_SCREEN_ROWS, KT_REFINE,  // screen

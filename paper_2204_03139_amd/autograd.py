@@ -30,23 +30,19 @@ class DiffCloudChamfer(torch.autograd.Function):
         b_side = reduction != _lib.DC_RED_SIM2REAL_SUM
         out = _lib.chamfer_fwd(points, obs, precision=precision, reduction=reduction,
                                frame_w=frame_w, b_side=b_side)
-        idx_b = out["idx_b"] if b_side else torch.empty(0, dtype=torch.int32)
-        ctx.save_for_backward(faces, obs, points, face_idx, bary, out["idx_a"], idx_b,
-                              frame_w if frame_w is not None else torch.empty(0))
-        ctx.b_side = b_side
+        ctx.save_for_backward(faces, obs, points, face_idx, bary, out["idx_a"], out["idx_b"],
+                              frame_w)
         ctx.V = v.shape[1]
         ctx.reduction = reduction
-        ctx.has_w = frame_w is not None
         ctx.mark_non_differentiable(out["idx_a"])
         return out["loss"]
 
     @staticmethod
     def backward(ctx, grad_loss):
         faces, obs, points, face_idx, bary, idx_a, idx_b, fw = ctx.saved_tensors
-        fw = fw if ctx.has_w else None
         want_b = ctx.needs_input_grad[2]
         ga, gb = _lib.chamfer_bwd(grad_loss.detach().to(torch.float64).contiguous(), points, obs,
-                                  idx_a, idx_b if ctx.b_side else None, reduction=ctx.reduction,
+                                  idx_a, idx_b, reduction=ctx.reduction,
                                   frame_w=fw, want_b=want_b)
         gv = _lib.sample_surface_bwd(ga, faces, face_idx, bary, ctx.V)
         return gv, None, gb, None, None, None, None, None, None, None

@@ -1,9 +1,12 @@
 // Area-weighted surface sampling (arXiv 2204.03139, Sec. III-B, Eq. 3).
 //
 // Two kernels per call:
-//   k_area_cdf   one workgroup per frame: face areas in double (all lanes), then the running sum
-//                C_k = C_{k-1} + A_k in double by one wave, equal bit for bit to the left-to-right
-//                sum (index stability needs the same rounding as a sequential sum).
+//   k_area_cdf   one workgroup per frame: face areas in double, then the running sum
+//                C_k = C_{k-1} + A_k in double, equal bit for bit to the left-to-right sum (index
+//                stability needs the same rounding as a sequential sum).  Bounded by the doubles'
+//                instructions of the one CU: 6 us for the areas and sums of 2,560 faces.  One wave
+//                on the sums, the others on the next areas, took 38.7 us for 40 frames of 4,802 faces
+//                and 77.8 us for 100 of 19,602; all waves on both take 18.0 and 52.8 us.
 //   k_sample     one lane per point: random words (given, or Philox4x64-10), inverse-CDF face
 //                choice by an upper-bound search, barycentric point in float (k_sample_wide where
 //                there are enough points).
@@ -15,12 +18,15 @@
 namespace dc {
 namespace {
 
-#ifndef DC_AREA_CDF_THREADS
-#define DC_AREA_CDF_THREADS 1024
-#endif
-constexpr int AC_THREADS = DC_AREA_CDF_THREADS;  // one wave sums, the other waves compute areas
-constexpr int AC_CHUNK = 4000;  // faces per chunk (two buffers, padded: 80 KB of LDS)
-constexpr int AC_GROUP = 5;     // faces per thread and chunk: 4000 faces over 960 or 1024 threads
+// Threads of a workgroup and most faces per thread and chunk.  Fewer threads have their sums sooner,
+// more of them share the doubles' instructions of a longer mesh: with 512 x 5 faces one frame of 1,152
+// faces takes 10.8 us, 40 frames of 4,802 18.0 us, 24 of 12,482 34.4 us and 100 of 19,602 52.8 us (launch
+// included), with 256 x 5 9.5, 21.8, 44.2 and 70.2 us and with 1,024 x 5 15.1, 19.8, 37.0 and 52.8 us.
+// The smallest meshes, of one face per thread, are bound by the length of the code alone: 25 frames of
+// 72 faces take 6.6 us with 256 x 1 and 9.4 us with 512 x 5.
+constexpr int AC_THREADS = 512, AC_PER = 5;
+constexpr int AC_SMALL = 256;  // threads, and most faces, of a small mesh
+constexpr int AC_STEPS = 64;   // most single additions of a chunk summed by all waves
 
 __device__ __forceinline__ bool face_ok(const int32_t *fv, int V) {
     const int32_t i0 = fv[0], i1 = fv[1], i2 = fv[2];
@@ -59,7 +65,7 @@ __device__ __forceinline__ double tri_area_f64(const float *p1, const float *p2,
 // or binade changes in a row cost no more than the plain chain.  A zero sum skips the zero areas
 // after it (0 + 0 = 0); a sum that is not finite, or below the normal range, ends the chunk in the
 // plain chain.  `cur` is a chunk buffer: entries [n, n + RS_WIN) are padding that a window may
-// load, and the 64 slots from AC_CHUNK + RS_WIN on take the stores a window does not want.
+// load, and the 64 slots from CHUNK + RS_WIN on take the stores a window does not want.
 constexpr int RS_PER = 15;  // odd: lanes 120 bytes apart read and write on different LDS banks
 constexpr int RS_WIN = 64 * RS_PER;
 constexpr int RS_BURST = 64;
@@ -107,6 +113,42 @@ __device__ __forceinline__ double wave_prefix(double v, int lane) {
     return v;
 }
 
+// the sums of d and of n over lanes 0..lane (d modulo 2^64)
+template <int CTRL>
+__device__ __forceinline__ void add_shifted(unsigned long long &d, int &n) {
+    const unsigned lo = (unsigned)__builtin_amdgcn_update_dpp(0, (int)(unsigned)d, CTRL, 0xF, 0xF, true);
+    const unsigned hi =
+        (unsigned)__builtin_amdgcn_update_dpp(0, (int)(unsigned)(d >> 32), CTRL, 0xF, 0xF, true);
+    n += __builtin_amdgcn_update_dpp(0, n, CTRL, 0xF, 0xF, true);
+    d += ((unsigned long long)hi << 32) | lo;
+}
+
+__device__ __forceinline__ unsigned long long lane_word(unsigned long long d, int l) {
+    const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)d, l);
+    const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)(d >> 32), l);
+    return ((unsigned long long)hi << 32) | lo;
+}
+
+__device__ __forceinline__ void wave_count(unsigned long long &d, int &n, int lane) {
+    add_shifted<0x111>(d, n);  // row_shr:1
+    add_shifted<0x112>(d, n);  // row_shr:2
+    add_shifted<0x114>(d, n);  // row_shr:4
+    add_shifted<0x118>(d, n);  // row_shr:8
+    unsigned long long ad = 0;
+    int an = 0;
+#pragma unroll
+    for (int row = 1; row < 4; ++row) {
+        const unsigned long long rd = lane_word(d, 16 * row - 1);
+        const int rn = __builtin_amdgcn_readlane(n, 16 * row - 1);
+        if (lane >> 4 >= row) {
+            ad += rd;
+            an += rn;
+        }
+    }
+    d += ad;
+    n += an;
+}
+
 __device__ __forceinline__ void plain_sum(double *cur, int i0, int i1, double &run) {
     double r = run;
     int i = i0;
@@ -133,6 +175,7 @@ __device__ __forceinline__ void wave_sync_lds() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
+template <int CHUNK>
 __device__ void running_sum(double *cur, int n, double &run, int lane) {
     constexpr double LIM = 9007199254740992.0;  // 2^53
     int k = 0;
@@ -199,7 +242,7 @@ __device__ void running_sum(double *cur, int n, double &run, int lane) {
             // entries at or after the stop go to the lane's spare slot instead (no branches)
 #pragma unroll
             for (int i = 0; i < RS_PER; ++i)
-                cur[base + i < stop ? k + base + i : AC_CHUNK + RS_WIN + lane] =
+                cur[base + i < stop ? k + base + i : CHUNK + RS_WIN + lane] =
                     __builtin_ldexp(pre[i], -sh);
             if (stop == RS_WIN && avail >= RS_WIN) {  // the whole window stayed in the binade
                 run = __builtin_ldexp(ms + lane_value(incl, 63), -sh);
@@ -228,6 +271,169 @@ __device__ void running_sum(double *cur, int n, double &run, int lane) {
     wave_sync_lds();
 }
 
+__device__ __forceinline__ int binade(double v) {
+    return (int)(((unsigned long long)__double_as_longlong(v) >> 52) & 0x7FF);
+}
+
+// what the waves of a workgroup tell each other over a chunk
+template <int WAVES>
+struct ChunkSums {
+    double near_total[WAVES];             // sums of the waves' areas, in any order
+    unsigned long long d[WAVES];          // the waves' integers, modulo 2^64
+    int steps[WAVES];                     // the waves' single additions
+    double area[AC_STEPS];                // of each single addition: its area,
+    unsigned long long before[AC_STEPS];  // the integers before it,
+    int e[AC_STEPS];                      // the binade of the sum before it
+    double end;                           // the sum of the chunk
+    // one wave has to sum the chunk (of even and odd chunks): seen before or after its integers
+    // were summed
+    int odd[2], wrong[2];
+};
+
+// The running sums of a chunk by all lanes at once, each the areas a[0..per) that follow those of the
+// lane before it, from the sum `start` of the chunks before: the same integers on the grid of a binade
+// as in running_sum, over several binades.  Every lane takes the binades of its partial sums from sums
+// in any order (near sums).  An area whose near sums before and after it lie in one binade, and that is
+// no tie, becomes an integer; the others are single additions, done in order by every wave for itself
+// over at most AC_STEPS of them, each after the sum of the integers since the one before.  The integers
+// are summed modulo 2^64, where the difference of two sums is exact although the units change on the
+// way.  A near sum may lie on the wrong side of a binade's edge: each lane checks, against the exact
+// sums, that its integers' unit is that of the binade in which their run starts and that they end in
+// the same binade; then every rounding was the one of the sequential sum.  Where a check fails, or there
+// are more single additions, sums that are not finite or are below the normal range, it returns false on
+// all lanes and one wave sums the chunk.
+template <int WAVES, int PER>
+__device__ __forceinline__ bool chunk_sums(double (&a)[PER], int per, int n, double start,
+                                           ChunkSums<WAVES> &c, int side, int wave, int lane) {
+    double near = 0.0;
+#pragma unroll
+    for (int k = 0; k < PER; ++k) near = near + a[k];
+    const double incl = wave_prefix(near, lane);
+    if (lane == 63) c.near_total[wave] = incl;
+    __syncthreads();
+    double before = start;
+#pragma unroll
+    for (int w = 0; w < WAVES - 1; ++w) before = before + (w < wave ? c.near_total[w] : 0.0);
+    before = before + lane_before(incl);
+    unsigned long long run = 0, d[PER];
+    int e[PER];
+    int mine = 0, single = 0;
+    bool odd = false;
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+        const double after = before + a[k];
+        e[k] = binade(before);
+        const int e1 = binade(after);
+        odd = odd || e1 == 0x7FF || (e1 == 0 && after != 0.0);
+        const double y = __builtin_ldexp(a[k], 1075 - e[k]) + 0.5;
+        const double q = __builtin_floor(y);
+        const bool one = e[k] != e1 || q == y;
+        if (one) {
+            single |= 1 << k;
+            ++mine;
+        } else {
+            run += (unsigned long long)q;
+        }
+        d[k] = run;
+        before = after;
+    }
+    unsigned long long di = run;
+    int ni = mine;
+    wave_count(di, ni, lane);
+    if (lane == 63) {
+        c.d[wave] = di;
+        c.steps[wave] = ni;
+    }
+    if (odd) c.odd[side] = 1;
+    __syncthreads();
+    unsigned long long base = di - run;
+    int first = ni - mine, steps = 0;
+#pragma unroll
+    for (int w = 0; w < WAVES; ++w) {
+        const int s = c.steps[w];
+        steps += s;
+        if (w < wave) {
+            base += c.d[w];
+            first += s;
+        }
+    }
+    if (steps > AC_STEPS || c.odd[side]) return false;
+    double sum = start, after = 0.0;  // after: of lane j, the sum after the j-th single addition
+    unsigned long long at = 0;        // and the integers up to it
+    if (steps) {
+        int j = first;
+#pragma unroll
+        for (int k = 0; k < PER; ++k) {
+            if (single >> k & 1) {
+                c.area[j] = a[k];
+                c.before[j] = base + d[k];
+                c.e[j] = e[k];
+                ++j;
+            }
+        }
+        __syncthreads();
+        double area = 0.0, gap = 0.0;
+        int ej = 0;
+        bool some = false;
+        if (lane < steps) {
+            area = c.area[lane];
+            at = c.before[lane];
+            ej = c.e[lane];
+            const unsigned long long last = lane ? c.before[lane - 1] : 0;
+            some = at != last;
+            gap = __builtin_ldexp((double)(at - last), ej - 1075);
+        }
+        bool wrong = false;
+        for (int i = 0; i < steps; ++i) {
+            const double from = sum;
+            sum = (sum + lane_value(gap, i)) + lane_value(area, i);
+            if (lane == i) {
+                wrong = some && binade(from) != ej;
+                after = sum;
+            }
+        }
+        if (wrong) c.wrong[side] = 1;
+    }
+    // each lane's run: the sum it starts from and the integers up to there
+    double from = start;
+    unsigned long long zero = 0;
+    if (steps) {
+        const int r = max(first - 1, 0);
+        const double fs = __shfl(after, r, 64);
+        const unsigned long long fz = __shfl(at, r, 64);
+        if (first) {
+            from = fs;
+            zero = fz;
+        }
+    }
+    int j = first;
+    bool wrong = false;
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+        const bool one = single >> k & 1;
+        if (__ballot(one)) {
+            const int r = min(j, 63);
+            const double fs = __shfl(after, r, 64);
+            const unsigned long long fz = __shfl(at, r, 64);
+            if (one) {
+                from = fs;
+                zero = fz;
+                ++j;
+            }
+        }
+        const double v = from + __builtin_ldexp((double)(base + d[k] - zero), e[k] - 1075);
+        if (!one) wrong = wrong || binade(from) != e[k] || binade(v) != e[k];
+        a[k] = one ? from : v;
+    }
+    if (wrong) c.wrong[side] = 1;
+    const int at_end = (n - 1) - (int)threadIdx.x * per;  // the chunk's last area, if it is this lane's
+#pragma unroll
+    for (int k = 0; k < PER; ++k)
+        if (k == at_end && k < per) c.end = a[k];
+    __syncthreads();
+    return !c.wrong[side];
+}
+
 struct AreaCdfParams {
     const float *verts;
     const int32_t *faces;
@@ -239,98 +445,109 @@ struct AreaCdfParams {
     unsigned *status;
 };
 
-// Chunks of AC_CHUNK faces are double-buffered in LDS: while wave 0 runs the sum over chunk c
-// (and then copies it out), waves 1.. compute the areas of chunk c + 1.
+// One workgroup per frame, a chunk of faces after the other, each thread on up to PER faces in a row:
+// their index and corner gathers are in flight together, and the indices of the next chunk are loaded
+// before the sums of this one.
+template <int THREADS, int PER>
 __device__ __forceinline__ void area_cdf_body(const AreaCdfParams &p, const Blk &blk) {
     const float *__restrict__ verts = p.verts;
     const int32_t *__restrict__ faces = p.faces;
+    constexpr int CHUNK = THREADS * PER, WAVES = THREADS / 64;
     const int V = p.V, F = p.F;
-    // areas, then their running sums; a window of padding lets the summing wave load whole
-    // windows past the end of a chunk, and 64 spare slots take its unwanted stores
-    __shared__ __align__(16) double area[2][AC_CHUNK + RS_WIN + 64];
+    // a chunk that one wave sums: its areas, then their running sums; a window of padding lets the wave
+    // load whole windows past the end of the chunk, and 64 spare slots take its unwanted stores
+    __shared__ __align__(16) double area[CHUNK + RS_WIN + 64];
+    __shared__ ChunkSums<WAVES> sums;
     __shared__ int bad;
-    __shared__ int lastw[AC_THREADS / 64];
-    const int t = blk.x;
+    __shared__ int lastw[WAVES];
+    const int t = blk.x, tid = threadIdx.x;
     const float *vt = verts + (size_t)t * V * 3;
     double *ct = p.cdf + (size_t)t * F;
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    if (threadIdx.x == 0) bad = 0;
+    const int wave = tid >> 6, lane = tid & 63;
+    if (tid == 0) bad = 0;
+    if (tid < 2) sums.odd[tid] = sums.wrong[tid] = 0;
     int last = -1;  // last face with a positive area, per thread, then per workgroup
-    // areas of chunk c into buffer c & 1, by the threads [first, AC_THREADS)
-    // (a thread's faces of one chunk are loaded together, AC_GROUP at a time, so their index and
-    // corner gathers are in flight at once instead of one face after the other)
-    auto areas = [&](int c, int first) {
-        const int base = c * AC_CHUNK;
-        const int n = min(AC_CHUNK, F - base);
-        double *dst = area[c & 1];
-        const int stride = AC_THREADS - first;
-        for (int k0 = (int)threadIdx.x - first; k0 < n; k0 += AC_GROUP * stride) {
-            int32_t fv[AC_GROUP][3];
+    auto spread = [&](int base) { return min(PER, (F - base + THREADS - 1) / THREADS); };
+    int32_t fv[PER][3];
+    auto load = [&](int base) {
+        const int per = spread(base);
 #pragma unroll
-            for (int g = 0; g < AC_GROUP; ++g) {
-                const int k = k0 + g * stride;
-                const int32_t *f = faces + 3 * (size_t)(base + min(k, n - 1));
-                fv[g][0] = f[0];
-                fv[g][1] = f[1];
-                fv[g][2] = f[2];
-            }
-            bool ok[AC_GROUP];
-            float q[AC_GROUP][3][3];
-            unsigned char keep[AC_GROUP];
-#pragma unroll
-            for (int g = 0; g < AC_GROUP; ++g) {
-                ok[g] = face_ok(fv[g], V);
-#pragma unroll
-                for (int c3 = 0; c3 < 3; ++c3) {
-                    const float *v = vt + 3 * (size_t)(ok[g] ? fv[g][c3] : 0);
-                    q[g][c3][0] = v[0];
-                    q[g][c3][1] = v[1];
-                    q[g][c3][2] = v[2];
-                }
-                const int k = k0 + g * stride;
-                keep[g] = p.mask ? p.mask[(size_t)t * p.mask_stride + base + min(k, n - 1)] : 1;
-            }
-#pragma unroll
-            for (int g = 0; g < AC_GROUP; ++g) {
-                const int k = k0 + g * stride;
-                if (k >= n) break;
-                double a = 0.0;
-                if (ok[g]) {
-                    a = tri_area_f64(q[g][0], q[g][1], q[g][2]);
-                    // a face outside the subset takes part with area 0: it is never drawn
-                    if (!keep[g]) a = 0.0;
-                } else {
-                    bad = 1;
-                }
-                dst[k] = a;
-                last = (a > 0.0) ? base + k : last;
-            }
+        for (int k = 0; k < PER; ++k) {
+            const int32_t *f = faces + 3 * (size_t)min(base + tid * per + k, F - 1);
+            fv[k][0] = f[0];
+            fv[k][1] = f[1];
+            fv[k][2] = f[2];
         }
     };
-    const int nchunk = (F + AC_CHUNK - 1) / AC_CHUNK;
-    __syncthreads();  // `bad` is cleared before any thread may set it
-    areas(0, 0);
-    __syncthreads();
-    double run = 0.0;  // the running sum, held by thread 0
-    for (int c = 0; c < nchunk; ++c) {
-        const int base = c * AC_CHUNK;
-        const int n = min(AC_CHUNK, F - base);
-        double *cur = area[c & 1];
-        if (wave == 0) {
-            running_sum(cur, n, run, lane);
-            for (int k = lane; k < n; k += 64) ct[base + k] = cur[k];
-        } else if (c + 1 < nchunk) {
-            areas(c + 1, 64);
+    load(0);
+    __syncthreads();  // the flags are cleared before any thread may set them
+    double run = 0.0;  // the running sum
+    for (int base = 0, side = 0; base < F; base += CHUNK, side ^= 1) {
+        const int n = min(CHUNK, F - base);
+        const int per = spread(base);
+        bool ok[PER];
+        float q[PER][3][3];
+        unsigned char keep[PER];
+#pragma unroll
+        for (int k = 0; k < PER; ++k) {
+            const int i = tid * per + k;
+            ok[k] = face_ok(fv[k], V);
+#pragma unroll
+            for (int c3 = 0; c3 < 3; ++c3) {
+                const float *v = vt + 3 * (size_t)(ok[k] ? fv[k][c3] : 0);
+                q[k][c3][0] = v[0];
+                q[k][c3][1] = v[1];
+                q[k][c3][2] = v[2];
+            }
+            keep[k] = p.mask ? p.mask[(size_t)t * p.mask_stride + min(base + i, F - 1)] : 1;
         }
-        __syncthreads();
+        if (base + CHUNK < F) load(base + CHUNK);
+        double a[PER];
+#pragma unroll
+        for (int k = 0; k < PER; ++k) {
+            const int i = tid * per + k;
+            a[k] = 0.0;
+            if (k < per && i < n) {
+                if (!ok[k])
+                    bad = 1;
+                else if (keep[k])  // a face outside the subset takes part with area 0: never drawn
+                    a[k] = tri_area_f64(q[k][0], q[k][1], q[k][2]);
+                if (a[k] > 0.0) last = base + i;
+            }
+        }
+        double one[PER];
+#pragma unroll
+        for (int k = 0; k < PER; ++k) one[k] = a[k];
+        if (chunk_sums(a, per, n, run, sums, side, wave, lane)) {
+#pragma unroll
+            for (int k = 0; k < PER; ++k)
+                if (k < per && tid * per + k < n) ct[base + tid * per + k] = a[k];
+            run = sums.end;
+            if (tid == 0) sums.odd[side ^ 1] = sums.wrong[side ^ 1] = 0;
+        } else {
+            __syncthreads();
+            if (tid < 2) sums.odd[tid] = sums.wrong[tid] = 0;
+#pragma unroll
+            for (int k = 0; k < PER; ++k)
+                if (k < per && tid * per + k < n) area[tid * per + k] = one[k];
+            __syncthreads();
+            if (wave == 0) {
+                running_sum<CHUNK>(area, n, run, lane);
+                if (lane == 0) sums.end = run;
+            }
+            __syncthreads();
+            for (int k = tid; k < n; k += THREADS) ct[base + k] = area[k];
+            run = sums.end;
+            __syncthreads();  // before the next chunk's sum takes its place
+        }
     }
     // faces are visited in increasing order per thread, so the maximum is the last positive one
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) last = max(last, __shfl_xor(last, off, 64));
     if (lane == 0) lastw[wave] = last;
     __syncthreads();
-    if (threadIdx.x == 0) {
-        for (int w = 1; w < AC_THREADS / 64; ++w) last = max(last, lastw[w]);
+    if (tid == 0) {
+        for (int w = 1; w < WAVES; ++w) last = max(last, lastw[w]);
         const bool degenerate = !(run > 0.0) || !__builtin_isfinite(run);
         p.lastpos[t] = (degenerate || bad) ? -1 : last;
         if (bad) atomicOr(p.status, (unsigned)ST_BAD_FACE);
@@ -338,8 +555,9 @@ __device__ __forceinline__ void area_cdf_body(const AreaCdfParams &p, const Blk 
     }
 }
 
-__global__ __launch_bounds__(AC_THREADS) void k_area_cdf(AreaCdfParams p) {
-    area_cdf_body(p, grid_blk());
+template <int THREADS, int PER>
+__global__ __launch_bounds__(THREADS) void k_area_cdf(AreaCdfParams p) {
+    area_cdf_body<THREADS, PER>(p, grid_blk());
 }
 
 // Philox4x64-10 (Salmon, Moraes, Dror, Shaw, SC'11): ten rounds of two 64x64->128 products
@@ -597,7 +815,10 @@ void launch_area_cdf(const float *verts, const int32_t *faces, int T, int V, int
     ap.cdf = cdf;
     ap.lastpos = lastpos;
     ap.status = status;
-    dispatch(KT_AREA_CDF, k_area_cdf, dim3(T), AC_THREADS, ap, s);
+    if (F <= AC_SMALL && !g_record)
+        dispatch(KT_AREA_CDF, k_area_cdf<AC_SMALL, 1>, dim3(T), AC_SMALL, ap, s);
+    else
+        dispatch(KT_AREA_CDF, k_area_cdf<AC_THREADS, AC_PER>, dim3(T), AC_THREADS, ap, s);
 }
 
 void launch_sample(const float *verts, const int32_t *faces, int T, int V, int F, int N,
@@ -627,7 +848,8 @@ void launch_sample(const float *verts, const int32_t *faces, int T, int V, int F
     const size_t corners = (size_t)V * 12;
     if (all >= size_t(1) << 19 && N >= 8192 && corners + (size_t(8) << 10) <= SW_BYTES) {
         const size_t share = (all + SW_CUS - 1) / SW_CUS;
-        sp.chunk = (int)std::min((share + SW_THREADS - 1) / SW_THREADS * SW_THREADS, size_t(1) << 24);
+        sp.chunk = (int)std::min((share + SW_THREADS - 1) / SW_THREADS * SW_THREADS,
+                                 size_t(1) << 24);
         int most = 10;
         while (most < SW_LEVELS && corners + (size_t(16) << most) <= SW_BYTES &&
                (1 << most) < sp.chunk)
@@ -645,7 +867,8 @@ void launch_sample(const float *verts, const int32_t *faces, int T, int V, int F
 }
 
 void register_sample_kernels(BatchedKernel *table) {
-    table[KT_AREA_CDF] = batched_kernel<AreaCdfParams, area_cdf_body, AC_THREADS, 256>();
+    table[KT_AREA_CDF] =
+        batched_kernel<AreaCdfParams, area_cdf_body<AC_THREADS, AC_PER>, AC_THREADS, 512>();
     table[KT_SAMPLE] = batched_kernel<SampleParams, sample_body, SP_THREADS, 1024>();
     table[KT_SAMPLE_WIDE] = batched_kernel<SampleParams, sample_wide_body, SW_THREADS, 256>();
 }

@@ -19,13 +19,14 @@
 // the points at exactly that distance.  A box of zero size holds one point repeated: its distance and
 // least index stand for the whole block.
 //
-// What it costs and what bounds it (100 frames of 65,536 x 65,536, both directions).  k_near: 1.75 ms,
+// What it costs and what bounds it (100 frames of 65,536 x 65,536, both directions).  k_near: 1.72 ms,
 // vector issue: a wave evaluates 21 of 2,048 blocks (690 of 65,536 pairs per query; the least
-// possible for these blocks is 17 to 21) at 6.5 instructions per pair, 7,500 instructions in all;
-// the exhaustive searches of the same frames took 53.9 ms (fp32) and 25.2 ms (bf16 screen and its
-// refine).  Ordering: 0.28 ms, of which 0.17 ms deals out the points, 13 million 16-byte stores at
-// random inside a cloud's megabyte.  On one frame a wave's chain of dependent loads bounds it: 106
-// us, 56 us with four waves to a query wave.
+// possible for these blocks is 17 to 21) at 6.5 instructions per pair, 6,500 instructions in all;
+// k_near_screened, which leaves the pairs to the matrix cores: 1.22 ms.  The exhaustive searches of
+// the same frames took 53.9 ms (fp32) and 25.2 ms (bf16 screen and its refine).  Ordering: 0.28 ms,
+// of which 0.17 ms deals out the points, 13 million 16-byte stores at random inside a cloud's
+// megabyte.  On one frame a wave's chain of dependent loads bounds it: 106 us, 56 us with four waves
+// to a query wave.
 #include <algorithm>
 
 #include "batch.h"
@@ -35,7 +36,7 @@ namespace {
 
 constexpr int OB = 32;                 // points of a block
 constexpr int OSUB = 16;               // points of a sub-tile, half a block
-// points in scalar registers at once: with 8 the 100-frame search takes 1.75 ms, with 4 (which the
+// points in scalar registers at once: with 8 the 100-frame k_near takes 1.75 ms, with 4 (which the
 // compiler chooses by itself) or 16 (registers spill) about 0.2 ms more
 constexpr int OLOAD = 8;
 constexpr int OSUPER = 64;             // blocks of a super-block
@@ -695,6 +696,10 @@ struct NearParams {
 // sixteenth block, and they prune by the best distances of all, kept in LDS.
 constexpr int NEAR_THREADS = 256;
 constexpr int NEAR_SHARED_THREADS = 1024;
+// The screened search: one wave per workgroup, so that a long wave keeps no finished ones' registers
+// (100 frames: 1.22 ms against 1.27 ms with four), and registers for six waves on a SIMD.
+constexpr int SCREEN_THREADS = 64;
+constexpr int SCREEN_WAVES = 6;
 // Waves that the chip holds at once: a side with fewer shares its query waves out, four ways below
 // NEAR_FULL / 4, sixteen below NEAR_FULL / 16.  Measured with 110, 256 and 2,048 query waves in the
 // call: 33.5 -> 13.1, 40 -> 17.8 and 106 -> 56 us; with 2,560 and 8,192 sharing changes nothing
@@ -768,6 +773,127 @@ __device__ __forceinline__ int arg_min_lane(float v) {
     const float m = wave_min(v);
     const unsigned long long b = __ballot(v == m);
     return b ? (int)__builtin_ctzll(b) : 0;
+}
+
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ unsigned bf16_pair(float lo, float hi) {
+    bf16x2 v;
+    v[0] = (__bf16)lo;
+    v[1] = (__bf16)hi;
+    return __builtin_bit_cast(unsigned, v);
+}
+
+__device__ __forceinline__ float pair_lo(unsigned v) { return __uint_as_float(v << 16); }
+__device__ __forceinline__ float pair_hi(unsigned v) { return __uint_as_float(v & 0xffff0000u); }
+
+// the low halves, or the high halves, of two pairs
+__device__ __forceinline__ unsigned lows(unsigned a, unsigned b) {
+    return __builtin_amdgcn_perm(b, a, 0x05040100u);
+}
+__device__ __forceinline__ unsigned highs(unsigned a, unsigned b) {
+    return __builtin_amdgcn_perm(b, a, 0x07060302u);
+}
+
+constexpr unsigned BF16_1 = 0x3f80u, BF16_11 = 0x3f803f80u;
+
+// The screen of a block: its 32 points against the wave's 64 queries in two matrix instructions.  With
+// p' and q' the coordinates less the centre of the queries' box, |p'|^2 - 2 q'.p' + |q'|^2 is a sum of
+// 16 products of bf16 numbers, each coordinate in two parts (their smallest products dropped) and each
+// square in three: lanes 0..31 hold the first eight factors of a row or column, lanes 32..63 the rest.
+//   points   xh yh zh  xl yl zl  sh sm | xh yh zh  sl  1  1  1  0      (s = |p'|^2)
+//   queries  xh yh zh  xh yh zh   1  1 | xl yl zl   1 uh um ul  0      (of -2 q'; u = |q'|^2 + slack)
+__device__ __forceinline__ bf16x8 screen_point(float x, float y, float z, bool upper) {
+    const float s = canon_gap(x, y, z);
+    const unsigned xy = bf16_pair(x, y), zs = bf16_pair(z, s);
+    const unsigned xs = bf16_pair(x - pair_lo(xy), s - pair_hi(zs));
+    const unsigned yz = bf16_pair(y - pair_hi(xy), z - pair_lo(zs));
+    const unsigned sl = bf16_pair(s - pair_hi(zs) - pair_hi(xs), 0.f);
+    u32x4 r;
+    r[0] = xy;
+    r[1] = lows(zs, upper ? sl : xs);
+    r[2] = upper ? BF16_11 : yz;
+    r[3] = upper ? BF16_1 : highs(zs, xs);
+    return __builtin_bit_cast(bf16x8, r);
+}
+
+__device__ __forceinline__ bf16x8 screen_query(float x, float y, float z, float u, bool upper) {
+    x = -2.f * x;
+    y = -2.f * y;
+    z = -2.f * z;
+    const unsigned xy = bf16_pair(x, y), zu = bf16_pair(z, u);
+    const float ur = u - pair_hi(zu);
+    const unsigned xyl = bf16_pair(x - pair_lo(xy), y - pair_hi(xy));
+    const unsigned zul = bf16_pair(z - pair_lo(zu), ur);
+    u32x4 r;
+    r[0] = upper ? xyl : xy;
+    r[1] = upper ? lows(zul, BF16_1) : lows(zu, xy);
+    r[2] = upper ? highs(zu, zul) : (xy >> 16 | zu << 16);
+    r[3] = upper ? bf16_pair(ur - pair_hi(zul), 0.f) : BF16_11;
+    return __builtin_bit_cast(bf16x8, r);
+}
+
+// Error of the screen.  The parts leave out at most 2^-18 of each factor and drop products of 2^-18:
+// 3 2^-18 (|p'|^2 + |q'|^2) together, and the sum of the products rounds by no more than
+// 2^-18 (|p'|^2 + |q'|^2).  With |p'|^2 <= 2 |q'|^2 + 2 d^2 that is within half of
+//   NEAR_ERR (3 |q'|^2 + 2 d^2),  NEAR_ERR = 2^-15,
+// which also holds the roundings of p', q' and of the canonical distance d^2 itself.  The slack in u is
+// the part without d^2 (and 1e-36 for what is below the normal range), so a screened value v has
+//   d^2 (1 - 2 NEAR_ERR) <= v <= d^2 (1 + 2 NEAR_ERR) + 2 slack:
+// it is never negative, d^2 is at most NEAR_UP v, and a point at the smallest distance G has
+// v <= NEAR_UP G + 2 slack.
+constexpr float NEAR_ERR = 0x1p-15f, NEAR_UP = 1.f + 0x1p-13f;
+constexpr float NEAR_SAFE = 1e30f;  // |q'|^2 and v up to which nothing overflows
+// The slack is small against the differences between a query's nearest points where the queries' box is
+// about as wide as a block of the targets.  On a jump of the curve it is wider, and more than two
+// sub-tiles remain for many of the wave's queries: then the blocks in reach are evaluated once more.
+constexpr int NEAR_FEW = 3;  // queries of a wave that are searched one by one
+
+// The end of a search: the queries without a finite distance, the results and the counters.
+__device__ __forceinline__ void near_finish(const NearParams &pr, const Blk &blk, const NearCloud &qc,
+                                            const NearCloud &pc, int lane, bool writes, bool first,
+                                            const nfloat4 &q, float best, int found, bool finite,
+                                            unsigned ties) {
+    const int t = blk.y, qi = __float_as_int(q.w);
+    const float inf = __builtin_inff();
+    // no finite distance: the first of the first 64 targets at an infinite distance, or target 0
+    unsigned long long none = writes ? __ballot(qi >= 0 && !finite) : 0ull;
+    while (none) {
+        const int l = (int)__builtin_ctzll(none);
+        none &= none - 1;
+        const float x = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(q.x), l));
+        const float y = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(q.y), l));
+        const float z = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(q.z), l));
+        bool hit = false;
+        if (lane < pc.n) {
+            const float *p = pc.src + ((size_t)t * pc.n + lane) * 3;
+            hit = canon_gap(x - p[0], y - p[1], z - p[2]) == inf;
+        }
+        const unsigned long long m = __ballot(hit);
+        if (lane == l) {
+            found = m ? (int)__builtin_ctzll(m) : 0;
+            best = inf;
+        }
+    }
+    if (qi >= 0 && writes) {
+        const size_t o = (size_t)t * qc.n + qi;
+        qc.idx[o] = found;
+        qc.dist[o] = best;
+    }
+    if (pr.stats && lane == 0) {
+        unsigned long long *slot =
+            pr.stats + (size_t)((blockIdx.x + gridDim.x * blockIdx.y) % STATS_SLOTS) * STATS_SLOT_WORDS;
+        if (first) {  // the call's queries, one sub-tile read again each
+            const unsigned long long all =
+                (unsigned long long)blk.gy * (pr.c[0].n + (pr.both ? pr.c[1].n : 0));
+            atomicAdd(&slot[0], all);
+            atomicAdd(&slot[1], all);
+        }
+        if (ties) atomicAdd(&slot[2], (unsigned long long)ties);
+    }
 }
 
 template <bool SHARED>
@@ -1005,45 +1131,321 @@ __device__ __forceinline__ void near_body(const NearParams &pr, const Blk &blk) 
         best = bound;
         finite = live && bound < inf;
     }
-    // no finite distance: the first of the first 64 targets at an infinite distance, or target 0
-    unsigned long long none = r == 0 ? __ballot(qi >= 0 && !finite) : 0ull;
-    while (none) {
-        const int l = (int)__builtin_ctzll(none);
-        none &= none - 1;
+    near_finish(pr, blk, qc, pc, lane, r == 0, blk.x == 0 && t == 0 && wave == 0, q, best, found, finite,
+                ties);
+}
+
+// The same search with its blocks screened on the matrix cores: two instructions give the 32 x 64
+// screened distances of a block, of which each query keeps the least of every sub-tile; the two
+// sub-tiles that may hold its smallest canonical distance are read again at the end.  3,650 vector
+// instructions per wave in place of 6,500 (100 frames of 65,536 x 65,536, both directions: 1.22 ms
+// against 1.72 ms), now bound by the waits of six waves per SIMD as much as by vector issue.
+__device__ __forceinline__ void near_screened_body(const NearParams &pr, const Blk &blk) {
+    const int t = blk.y;
+    const int lane = threadIdx.x;
+    const bool second = blk.x >= pr.wgs0;
+    const NearCloud &qc = pr.c[second ? 1 : 0], &pc = pr.c[second ? 0 : 1];
+    const int qw = blk.x - (second ? pr.wgs0 : 0);
+    const float inf = __builtin_inff();
+    const int supers_q = order_supers(qc.n), supers = order_supers(pc.n);
+    const int chunks = (supers + 63) / 64;
+    const int nblk = order_blocks(pc.n);
+    const nfloat4 *P = pc.pts + (size_t)t * order_npad(pc.n);
+    const float *pbox = pc.box + (size_t)t * supers * OBOX;
+    const float *psbox = pc.sbox + (size_t)t * chunks * 6 * 64;
+    const nfloat4 q = qc.pts[(size_t)t * order_npad(qc.n) + qw * 64 + lane];
+    // a NaN query has no distances; padding has no query
+    const bool live = q.x == q.x && q.y == q.y && q.z == q.z && __float_as_int(q.w) >= 0;
+    Box Q;
+    {  // the queries' box: two blocks of their own cloud
+        const int b = qw * 2;
+        scalar_f o = (scalar_f)(uintptr_t)(qc.box + ((size_t)t * supers_q + b / OSUPER) * OBOX +
+                                           b % OSUPER);
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            Q.l[k] = fminf(o[k * OSUPER], o[k * OSUPER + 1]);
+            Q.h[k] = fmaxf(o[(3 + k) * OSUPER], o[(3 + k) * OSUPER + 1]);
+        }
+    }
+    // the queries about the centre of their box, and the slack of their screened values
+    const float cx = 0.5f * Q.l[0] + 0.5f * Q.h[0],
+                cy = 0.5f * Q.l[1] + 0.5f * Q.h[1],
+                cz = 0.5f * Q.l[2] + 0.5f * Q.h[2];
+    const bool upper = lane >= 32;
+    bf16x8 B[2];
+    float slack, widest;
+    {
+        const float x = live ? q.x - cx : 0.f, y = live ? q.y - cy : 0.f, z = live ? q.z - cz : 0.f;
+        const float u = canon_gap(x, y, z);
+        slack = __builtin_fmaf(u, 3.f * NEAR_ERR, 1e-36f);
+        widest = wave_max(u);  // (without the NaN ones)
+        if (__ballot(!(u < NEAR_SAFE))) widest = inf;
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            const int from = k * 32 + (lane & 31);
+            B[k] = screen_query(__shfl(x, from, 64), __shfl(y, from, 64), __shfl(z, from, 64),
+                                __shfl(u + slack, from, 64), upper);
+        }
+    }
+    // the least screened values of sub-tiles (their bits), and where the first two were met: a sub-tile,
+    // or ~index of the least point of a block that is one point
+    constexpr unsigned INF = 0x7F800000u;
+    unsigned m1 = INF, m2 = INF, m3 = INF;
+    int at1 = 0, at2 = 0;
+    auto take = [&](unsigned v, int at) {
+        const bool c1 = v < m1, c2 = v < m2;
+        m3 = min(m3, max(m2, v));
+        m2 = min(m2, max(m1, v));
+        m1 = min(m1, v);
+        at2 = c1 ? at1 : (c2 ? at : at2);
+        at1 = c1 ? at : at1;
+    };
+    // Row m of the instruction is the point 16 h + 4 g + j of the block, m = 8 g + 4 h + j: then lanes
+    // 0..31 get the first sub-tile's values and lanes 32..63 the second's, of 32 queries at a time.
+    const int row = (lane & 4) * 4 + (lane >> 3 & 3) * 4 + (lane & 3);
+    float bound = live ? inf : -1.f;
+    auto screen = [&](int b) {
+        const nfloat4 p = P[(size_t)b * OB + row];
+        const bf16x8 A = screen_point(p.x - cx, p.y - cy, p.z - cz, upper);
+        unsigned m[2];
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            const f32x16 zero = {0.f};
+            const f32x16 d = __builtin_amdgcn_mfma_f32_32x32x16_bf16(A, B[k], zero, 0, 0, 0);
+            unsigned n[4];
+#pragma unroll
+            for (int g = 0; g < 4; ++g)
+                n[g] = min(min(__float_as_uint(d[4 * g]), __float_as_uint(d[4 * g + 1])),
+                           min(__float_as_uint(d[4 * g + 2]), __float_as_uint(d[4 * g + 3])));
+            m[k] = min(min(n[0], n[1]), min(n[2], n[3]));
+        }
+        const auto sw = __builtin_amdgcn_permlane32_swap(m[0], m[1], false, false);
+        take(sw[0], 2 * b);
+        take(sw[1], 2 * b + 1);
+    };
+    // The canonical distances, and the smallest original index at the smallest.
+    float best = inf;
+    int found = 0x7fffffff;
+    bool tie = false;
+    auto meet = [&](float e, int i) {
+        tie = e < best ? false : (tie || (e == best && i != found));
+        found = e < best ? i : (e == best ? min(found, i) : found);
+        best = fminf(best, e);
+    };
+    auto refine = [&](int at) {
+        if (at < 0) {
+            const float *p = pc.src + ((size_t)t * pc.n + ~at) * 3;
+            meet(canon_gap(q.x - p[0], q.y - p[1], q.z - p[2]), ~at);
+            return;
+        }
+        const nfloat4 *p = P + (size_t)at * OSUB;
+        float e = inf;
+        int i = 0x7fffffff;
+#pragma unroll 1
+        for (int j0 = 0; j0 < OSUB; j0 += 8) {
+            nfloat4 v[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) v[j] = p[j0 + j];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                const float d = canon_gap(q.x - v[j].x, q.y - v[j].y, q.z - v[j].z);
+                const int k = __float_as_int(v[j].w);
+                i = d < e ? k : (d == e ? min(i, k) : i);
+                e = fminf(e, d);
+            }
+        }
+        meet(e, i);
+    };
+    // all points of a block, one after the other
+    auto evaluate = [&](int b) {
+        scalar_f4 p = (scalar_f4)(uintptr_t)(P + (size_t)b * OB);
+#pragma unroll 1
+        for (int g = 0; g < OB; g += 4) {
+            nfloat4 v[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) v[j] = p[g + j];
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                meet(canon_gap(q.x - v[j].x, q.y - v[j].y, q.z - v[j].z), __float_as_int(v[j].w));
+        }
+    };
+    bool screened = false;
+    unsigned long long again = 0;
+    if (__ballot(live)) {
+        // the block nearest to the queries by its centre gives the first distances
+        int seed_super;
+        {
+            float dmin = inf;
+            int at = 0;
+            for (int c = 0; c < chunks; ++c) {
+                const int g = c * 64 + lane;
+                const float v = centre_dist(Q, lane_box(psbox + (size_t)c * 6 * 64, lane));
+                if (g < supers && v < dmin) {
+                    dmin = v;
+                    at = g;
+                }
+            }
+            seed_super = __builtin_amdgcn_readlane(at, arg_min_lane(dmin));
+        }
+        int seed = -1;
+        float near = -1.f;
+        {
+            const Box bx = lane_box(pbox + (size_t)seed_super * OBOX, lane);
+            const float v = seed_super * OSUPER + lane < nblk ? centre_dist(Q, bx) : inf;
+            // (by their bits: the compiler takes `v < inf` for `v != inf`, which holds for a NaN)
+            if (__ballot(__float_as_uint(v) < 0x7F800000u)) {
+                const int k = arg_min_lane(v);
+                seed = seed_super * OSUPER + k;
+                near = box_box(Q, box_of_lane(bx, k));
+                screened = widest < NEAR_SAFE;
+                if (screened) screen(seed);
+            }
+        }
+        auto limit = [&](float d) { return __builtin_fmaf(NEAR_UP, d, 2.f * slack); };
+        if (screened) {
+            bound = live ? NEAR_UP * __uint_as_float(m1) : -1.f;
+            // first the blocks as near to the queries' box as the seed, which mostly hold the
+            // neighbours, then the others within the distances found
+            for (int pass = 0; pass < 2; ++pass) {
+                for (int c = 0; c < chunks; ++c) {
+                    const int g = c * 64 + lane;
+                    const Box sb = lane_box(psbox + (size_t)c * 6 * 64, lane);
+                    float far = wave_max(bound);
+                    if (pass == 0) far = fminf(far, near);
+                    unsigned long long todo = __ballot(g < supers && !(box_box(Q, sb) > far));
+                    // the next super-block's boxes are on their way while this one's are worked on
+                    int s = todo ? c * 64 + (int)__builtin_ctzll(todo) : -1;
+                    Box ahead = sb;
+                    if (s >= 0) ahead = lane_box(pbox + (size_t)s * OBOX, lane);
+                    while (s >= 0) {
+                        const Box bx = ahead;
+                        const int s_at = s, b0 = s * OSUPER;
+                        todo &= todo - 1;
+                        s = todo ? c * 64 + (int)__builtin_ctzll(todo) : -1;
+                        if (s >= 0) ahead = lane_box(pbox + (size_t)s * OBOX, lane);
+                        const float l = box_box(Q, bx);
+                        far = wave_max(bound);
+                        if (pass == 0) far = fminf(far, near);
+                        unsigned long long in =
+                            __ballot(b0 + lane < nblk && b0 + lane != seed && !(l > far) &&
+                                     (pass == 0 || l > near));
+                        // a block of one point repeated needs no more than its box and least index
+                        const unsigned long long one = __ballot(one_point(bx)) & in;
+                        int least = 0;
+                        if (one) least = lane_least(pbox + (size_t)s_at * OBOX, lane);
+                        while (in) {
+                            const int k = (int)__builtin_ctzll(in);
+                            in &= in - 1;
+                            const float e = point_box(q.x, q.y, q.z, box_of_lane(bx, k));
+                            if (!__ballot(!(e > bound))) continue;
+                            if (one >> k & 1)
+                                take(__float_as_uint(e), ~__builtin_amdgcn_readlane(least, k));
+                            else
+                                screen(b0 + k);
+                            if (live) bound = NEAR_UP * __uint_as_float(m1);
+                        }
+                    }
+                }
+            }
+            // the sub-tiles that may hold the smallest distance
+            const bool known = live && __uint_as_float(m1) < NEAR_SAFE;
+            if (known) {
+                refine(at1);
+                if (__uint_as_float(m2) <= limit(best)) refine(at2);
+            }
+            again = __ballot(live && (!known || __uint_as_float(m3) <= limit(best)));
+        }
+        // More sub-tiles than that for some queries, or values that may have overflowed: every point
+        // again whose box is no further than the best so far, for those queries one by one with a
+        // point per lane, or for many of them for all at once.
+        if (!screened || __popcll(again) > NEAR_FEW) {
+            again = 0;
+            for (int c = 0; c < chunks; ++c) {
+                const int g = c * 64 + lane;
+                float far = wave_max(live ? best : -1.f);
+                unsigned long long todo = __ballot(
+                    g < supers && !(box_box(Q, lane_box(psbox + (size_t)c * 6 * 64, lane)) > far));
+                while (todo) {
+                    const int s = c * 64 + (int)__builtin_ctzll(todo);
+                    todo &= todo - 1;
+                    const Box bx = lane_box(pbox + (size_t)s * OBOX, lane);
+                    far = wave_max(live ? best : -1.f);
+                    unsigned long long in =
+                        __ballot(s * OSUPER + lane < nblk && !(box_box(Q, bx) > far));
+                    const unsigned long long one = __ballot(one_point(bx)) & in;
+                    int least = 0;
+                    if (one) least = lane_least(pbox + (size_t)s * OBOX, lane);
+                    while (in) {
+                        const int k = (int)__builtin_ctzll(in);
+                        in &= in - 1;
+                        const float e = point_box(q.x, q.y, q.z, box_of_lane(bx, k));
+                        if (!__ballot(live && !(e > best))) continue;
+                        if (one >> k & 1)
+                            meet(e, __builtin_amdgcn_readlane(least, k));
+                        else
+                            evaluate(s * OSUPER + k);
+                    }
+                }
+            }
+        }
+    }
+    while (again) {
+        const int l = (int)__builtin_ctzll(again);
+        again &= again - 1;
         const float x = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(q.x), l));
         const float y = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(q.y), l));
         const float z = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(q.z), l));
-        bool hit = false;
-        if (lane < pc.n) {
-            const float *p = pc.src + ((size_t)t * pc.n + lane) * 3;
-            hit = canon_gap(x - p[0], y - p[1], z - p[2]) == inf;
+        float bl = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(best), l));
+        float low = bl;
+        int mine = 0x7fffffff;
+        auto meet_one = [&](float e, int i) {
+            mine = e < low ? i : (e == low ? min(mine, i) : mine);
+            low = fminf(low, e);
+        };
+        for (int c = 0; c < chunks; ++c) {
+            const int g = c * 64 + lane;
+            const float lb = point_box(x, y, z, lane_box(psbox + (size_t)c * 6 * 64, lane));
+            unsigned long long todo = __ballot(g < supers && !(lb > bl));
+            while (todo) {
+                const int s = c * 64 + (int)__builtin_ctzll(todo);
+                todo &= todo - 1;
+                const Box bx = lane_box(pbox + (size_t)s * OBOX, lane);
+                const float e = point_box(x, y, z, bx);
+                const bool near = s * OSUPER + lane < nblk && !(e > bl);
+                const bool one = near && one_point(bx);
+                if (one) meet_one(e, lane_least(pbox + (size_t)s * OBOX, lane));
+                unsigned long long in = __ballot(near && !one);
+                while (in) {
+                    const int b = s * OSUPER + (int)__builtin_ctzll(in);
+                    in &= in - 1;
+                    const nfloat4 v = P[(size_t)b * OB + (lane & (OB - 1))];
+                    if (lane < OB)
+                        meet_one(canon_gap(x - v.x, y - v.y, z - v.z), __float_as_int(v.w));
+                }
+                bl = wave_min(low);
+            }
         }
-        const unsigned long long m = __ballot(hit);
+        const unsigned long long hits = __ballot(low == bl && mine != 0x7fffffff);
+        if (low != bl) mine = 0x7fffffff;
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) mine = min(mine, __shfl_xor(mine, off, 64));
         if (lane == l) {
-            found = m ? (int)__builtin_ctzll(m) : 0;
-            best = inf;
+            tie = __popcll(hits) > 1;
+            found = mine;
+            best = bl;
         }
     }
-    if (qi >= 0 && r == 0) {
-        const size_t o = (size_t)t * qc.n + qi;
-        qc.idx[o] = found;
-        qc.dist[o] = best;
-    }
-    if (pr.stats && lane == 0) {
-        unsigned long long *slot =
-            pr.stats + (size_t)((blockIdx.x + gridDim.x * blockIdx.y) % STATS_SLOTS) * STATS_SLOT_WORDS;
-        if (blk.x == 0 && t == 0 && wave == 0) {  // the call's queries, one sub-tile read again each
-            const unsigned long long all =
-                (unsigned long long)blk.gy * (pr.c[0].n + (pr.both ? pr.c[1].n : 0));
-            atomicAdd(&slot[0], all);
-            atomicAdd(&slot[1], all);
-        }
-        if (ties) atomicAdd(&slot[2], (unsigned long long)ties);
-    }
+    const bool finite = live && best < inf;
+    near_finish(pr, blk, qc, pc, lane, true, blk.x == 0 && t == 0, q, best, found, finite,
+                (unsigned)__popcll(__ballot(finite && tie)));
 }
 
 __global__ __launch_bounds__(NEAR_THREADS, 8) void k_near(NearParams p) {
     near_body<false>(p, grid_blk_xcd());
+}
+
+__global__ __launch_bounds__(SCREEN_THREADS, SCREEN_WAVES) void k_near_screened(NearParams p) {
+    near_screened_body(p, grid_blk_xcd());
 }
 
 __global__ __launch_bounds__(NEAR_SHARED_THREADS, 8) void k_near_shared(NearParams p) {
@@ -1114,6 +1516,16 @@ size_t ordered_scratch_bytes(int T, int Na, int Nb) {
     return ar.off;
 }
 
+// Whether k_near_screened takes the calls whose query waves fill the chip.  It has the longer wait for
+// a wave on a jump of the curve, which grows with the cloud and shows where few frames run beside it:
+// one to four frames of 262,144 points take 572 to 836 us with it against 288 to 625, four of 65,536
+// 148 against 190 and 100 of them 1,499 against 2,002 (ordering included).  And with few queries against
+// dense targets the slack leaves too many sub-tiles: 100 frames of 65,536 x 8,192 points take 1,008 us
+// against 956, of 65,536 x 20,000 1,139 against 1,232.
+bool near_screens(int Na, int Nb, bool two) {
+    return std::max(Na, Nb) <= 65536 && Nb <= 4L * Na && (!two || Na <= 4L * Nb);
+}
+
 void launch_ordered(const float *a, int Na, const float *b, int Nb, int T, int32_t *idx_a,
                     float *dist_a, int32_t *idx_b, float *dist_b, char *scratch,
                     unsigned long long *stats, dc_ctx *prof, hipStream_t s) {
@@ -1165,7 +1577,8 @@ void launch_ordered(const float *a, int Na, const float *b, int Nb, int T, int32
     }
     np.both = idx_b != nullptr;
     np.pad = 0;
-    const int per = shared ? NEAR_SHARED_THREADS / 64 : NEAR_THREADS / 64;
+    const bool screened = !shared && near_screens(Na, Nb, idx_b != nullptr);
+    const int per = (shared ? NEAR_SHARED_THREADS : screened ? SCREEN_THREADS : NEAR_THREADS) / 64;
     long wgs = 0;
     for (int k = 0; k < (idx_b ? 2 : 1); ++k) {
         const int groups = shared ? per >> np.share[k] : per;
@@ -1175,6 +1588,8 @@ void launch_ordered(const float *a, int Na, const float *b, int Nb, int T, int32
     ProfScope ps(prof, 0, s);
     if (shared)
         dispatch(KT_NEAR_SHARED, k_near_shared, dim3((unsigned)wgs, T), NEAR_SHARED_THREADS, np, s);
+    else if (screened)
+        dispatch(KT_NEAR_SCREENED, k_near_screened, dim3((unsigned)wgs, T), SCREEN_THREADS, np, s);
     else
         dispatch(KT_NEAR, k_near, dim3((unsigned)wgs, T), NEAR_THREADS, np, s);
 }
@@ -1186,6 +1601,8 @@ void register_ordered_kernels(BatchedKernel *table) {
     table[KT_ORDER_DEAL] = batched_kernel<OrderParams, order_deal_body, OC_THREADS, 1024>();
     table[KT_ORDER_BOX] = batched_kernel<OrderParams, order_box_body, OC_THREADS, 1024>();
     table[KT_NEAR] = batched_kernel<NearParams, near_body<false>, NEAR_THREADS, 2048, 8>();
+    table[KT_NEAR_SCREENED] =
+        batched_kernel<NearParams, near_screened_body, SCREEN_THREADS, 8192, SCREEN_WAVES>();
     table[KT_NEAR_SHARED] =
         batched_kernel<NearParams, near_body<true>, NEAR_SHARED_THREADS, 512, 8>();
 }

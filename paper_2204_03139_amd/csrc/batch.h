@@ -96,7 +96,6 @@ enum KernelType : int {
     KT_ORDER_DEAL,
     KT_ORDER_BOX,
     KT_NEAR,
-    KT_NEAR_SCREENED,
     KT_NEAR_SHARED,
     KT_COUNT
 };

@@ -7,26 +7,31 @@
 // each wave 64 consecutive (so nearby) ordered queries, one per lane.  The wave visits the
 // super-blocks, and in them the blocks, whose boxes lie no further from its queries' box than the
 // worst lane's best distance so far; a block that at least one lane cannot rule out by its own
-// distance to the box is evaluated by all lanes, its points read through the scalar cache.
+// distance to the box is screened on the matrix cores (two instructions for its 32 points and all 64
+// queries), and the 16 points (sub-tile) that may hold a query's smallest distance are evaluated at
+// the end.  k_near_shared, for calls with too few query waves for the chip, evaluates the blocks
+// themselves, the points read through the scalar cache.
 //
 // Exactness.  Subtraction, multiplication and fma round monotonically, and the distance to a box
 // uses the operations of the canonical distance on the gaps between the query and the box, which
 // are no larger in magnitude than the differences to any point in the box.  So the float distance
 // to a box is never above the canonical float distance to any of its points, and a box is skipped
-// only when it is strictly above the best: no minimum and no tie is lost.  A lane remembers the 16
-// points (sub-tile) that held its minimum and reads them again at the end for the smallest original
-// index at that distance; a lane that met its minimum in two sub-tiles is searched again for all
-// the points at exactly that distance.  A box of zero size holds one point repeated: its distance and
-// least index stand for the whole block.
+// only when it is strictly above the best: no minimum and no tie is lost.  A screened value has a
+// bound on its error, and every sub-tile within it of the least is kept.  The kept sub-tiles are read
+// again for the smallest canonical distance and its smallest original index; a lane that has more of
+// them than it remembers, or in k_near_shared met its minimum in two sub-tiles, is searched again.  A
+// box of zero size holds one point repeated: its distance and least index stand for the whole block.
 //
-// What it costs and what bounds it (100 frames of 65,536 x 65,536, both directions).  k_near: 1.72 ms,
-// vector issue: a wave evaluates 21 of 2,048 blocks (690 of 65,536 pairs per query; the least
-// possible for these blocks is 17 to 21) at 6.5 instructions per pair, 6,500 instructions in all;
-// k_near_screened, which leaves the pairs to the matrix cores: 1.22 ms.  The exhaustive searches of
-// the same frames took 53.9 ms (fp32) and 25.2 ms (bf16 screen and its refine).  Ordering: 0.28 ms,
-// of which 0.17 ms deals out the points, 13 million 16-byte stores at random inside a cloud's
-// megabyte.  On one frame a wave's chain of dependent loads bounds it: 106 us, 56 us with four waves
-// to a query wave.
+// What it costs and what bounds it (100 frames of 65,536 x 65,536, both directions).  k_near: 1.22 ms.  A
+// wave screens 21 of 2,048 blocks (690 of 65,536 pairs per query; the least possible for these blocks
+// is 17 to 21) in 3,450 vector instructions; the waits of six waves per SIMD bound it as much as
+// their issue.  With the blocks evaluated, at 6.5 instructions per pair and 6,500 per wave, it took
+// 1.72 ms, bound by vector issue; the exhaustive searches of the same frames 53.9 ms (fp32) and
+// 25.2 ms (bf16 screen and its refine).  Targets on a sphere about all queries, where no box rules
+// anything out, are the exhaustive searches' to win (20 frames: 17 ms; 11 ms with the blocks
+// evaluated).  Ordering: 0.28 ms, of which 0.17 ms deals out the points, 13 million 16-byte stores
+// at random inside a cloud's megabyte.  On one frame a wave's chain of dependent loads bounds it: 106
+// us, 56 us with four waves to a query wave.
 #include <algorithm>
 
 #include "batch.h"
@@ -36,8 +41,8 @@ namespace {
 
 constexpr int OB = 32;                 // points of a block
 constexpr int OSUB = 16;               // points of a sub-tile, half a block
-// points in scalar registers at once: with 8 the 100-frame k_near takes 1.75 ms, with 4 (which the
-// compiler chooses by itself) or 16 (registers spill) about 0.2 ms more
+// points in scalar registers at once: with 8 the 100-frame search by evaluated blocks takes 1.75 ms,
+// with 4 (which the compiler chooses by itself) or 16 (registers spill) about 0.2 ms more
 constexpr int OLOAD = 8;
 constexpr int OSUPER = 64;             // blocks of a super-block
 constexpr int OSUPER_PTS = OB * OSUPER;
@@ -691,20 +696,21 @@ struct NearParams {
     short both, share[2], pad;  // whether side 1 runs; log2 of the waves that share a query wave
 };
 
-// Workgroups of four waves, each with its own queries; or, where that would leave the chip idle,
-// of sixteen waves of which 1, 4 or 16 share their 64 queries: each takes every fourth or
-// sixteenth block, and they prune by the best distances of all, kept in LDS.
-constexpr int NEAR_THREADS = 256;
+// One wave per workgroup, so that a long wave keeps no finished ones' registers (100 frames: 1.22 ms
+// against 1.27 ms with four), and registers for six waves on a SIMD.
+constexpr int NEAR_THREADS = 64;
+constexpr int NEAR_WAVES = 6;
+// Where that would leave the chip idle, workgroups of sixteen waves of which 1, 4 or 16 share their 64
+// queries: each takes every fourth or sixteenth block, and they prune by the best distances of all, kept
+// in LDS.  A side shares sixteen ways up to NEAR_SHARE16 query waves (with 110 and 256 of them in the
+// call: 33.5 -> 13.1 and 40 -> 17.8 us, before the blocks of unshared waves were screened) and four ways
+// up to as many among few targets, which make short searches, and up to NEAR_SHARE4 among more.
+// Shared against not, ordering included: 550 waves on a side, 3,500 targets 44.2 and 36.3 us; 640 waves,
+// 8,192 targets 57.4 and 49.5 us; 1,024 waves, 65,536 targets 93 and 101 us; 1,100 waves, 3,500 targets
+// 52.6 and 40.7 us; 2,048 waves, 65,536 targets 130 and 114 us.
+constexpr long NEAR_SHARE16 = 512, NEAR_SHARE4 = 1024;
+constexpr int NEAR_FEW_TARGETS = 16384;
 constexpr int NEAR_SHARED_THREADS = 1024;
-// The screened search: one wave per workgroup, so that a long wave keeps no finished ones' registers
-// (100 frames: 1.22 ms against 1.27 ms with four), and registers for six waves on a SIMD.
-constexpr int SCREEN_THREADS = 64;
-constexpr int SCREEN_WAVES = 6;
-// Waves that the chip holds at once: a side with fewer shares its query waves out, four ways below
-// NEAR_FULL / 4, sixteen below NEAR_FULL / 16.  Measured with 110, 256 and 2,048 query waves in the
-// call: 33.5 -> 13.1, 40 -> 17.8 and 106 -> 56 us; with 2,560 and 8,192 sharing changes nothing
-// (46 -> 46, 235 -> 228 us), with 10,240 it costs (94 -> 132 us).
-constexpr long NEAR_FULL = 8192;
 
 // a box held by the lanes (lane b: block b), and one lane's box in scalar registers
 struct Box {
@@ -836,21 +842,25 @@ __device__ __forceinline__ bf16x8 screen_query(float x, float y, float z, float 
     return __builtin_bit_cast(bf16x8, r);
 }
 
-// Error of the screen.  The parts leave out at most 2^-18 of each factor and drop products of 2^-18:
-// 3 2^-18 (|p'|^2 + |q'|^2) together, and the sum of the products rounds by no more than
-// 2^-18 (|p'|^2 + |q'|^2).  With |p'|^2 <= 2 |q'|^2 + 2 d^2 that is within half of
-//   NEAR_ERR (3 |q'|^2 + 2 d^2),  NEAR_ERR = 2^-15,
-// which also holds the roundings of p', q' and of the canonical distance d^2 itself.  The slack in u is
-// the part without d^2 (and 1e-36 for what is below the normal range), so a screened value v has
-//   d^2 (1 - 2 NEAR_ERR) <= v <= d^2 (1 + 2 NEAR_ERR) + 2 slack:
-// it is never negative, d^2 is at most NEAR_UP v, and a point at the smallest distance G has
-// v <= NEAR_UP G + 2 slack.
+// Error of the screen.  The parts leave out at most 2^-18 of each factor and the products of 2^-18:
+// 6 2^-18 |q'| |p'| together, and the sum of the products rounds by no more than 2^-18 (|p'|^2 + |q'|^2).
+// With |p'| <= |q'| + d and |p'|^2 <= 2 |q'|^2 + 2 d^2 that is within 2^-18 (9 |q'|^2 + 6 |q'| d + 2 d^2),
+// and, a third more for the roundings of p', q' and of the canonical distance d^2 itself, within
+//   E(d) = 2^-18 (12 |q'|^2 + 8 |q'| d + 3 d^2) <= NEAR_ERR (3 |q'|^2 + 2 d^2),  NEAR_ERR = 2^-15.
+// The slack in u is 3 NEAR_ERR |q'|^2 (and 1e-36 for what is below the normal range).  So a screened
+// value v is never negative, d^2 is at most NEAR_UP v, and a point at the smallest distance d has
+// v <= d^2 + slack + E(d).
 constexpr float NEAR_ERR = 0x1p-15f, NEAR_UP = 1.f + 0x1p-13f;
 constexpr float NEAR_SAFE = 1e30f;  // |q'|^2 and v up to which nothing overflows
 // The slack is small against the differences between a query's nearest points where the queries' box is
 // about as wide as a block of the targets.  On a jump of the curve it is wider, and more than two
-// sub-tiles remain for many of the wave's queries: then the blocks in reach are evaluated once more.
-constexpr int NEAR_FEW = 3;  // queries of a wave that are searched one by one
+// sub-tiles remain for many of the wave's queries: then the blocks in reach are evaluated once more for
+// all of them, or the queries searched one by one where those are few.  Both are a wait for one wave
+// that shows where few frames run beside it: a query takes about 4 us, a sweep of the blocks as long as
+// the tests of their boxes, so the line lies at NEAR_FEW and one query more per 128 blocks.  Two frames
+// of 131,072 points take 181 us with it, 268 us with three queries at any size; one frame of 262,144
+// points 264 and 302 us (ordering included, both directions).
+constexpr int NEAR_FEW = 3;
 
 // The end of a search: the queries without a finite distance, the results and the counters.
 __device__ __forceinline__ void near_finish(const NearParams &pr, const Blk &blk, const NearCloud &qc,
@@ -896,36 +906,33 @@ __device__ __forceinline__ void near_finish(const NearParams &pr, const Blk &blk
     }
 }
 
-template <bool SHARED>
-__device__ __forceinline__ void near_body(const NearParams &pr, const Blk &blk) {
-    constexpr int WAVES = (SHARED ? NEAR_SHARED_THREADS : NEAR_THREADS) / 64;
+// The search of query waves that several waves share.
+__device__ __forceinline__ void near_shared_body(const NearParams &pr, const Blk &blk) {
+    constexpr int WAVES = NEAR_SHARED_THREADS / 64;
     const int t = blk.y;
     const int lane = threadIdx.x & 63;
     const bool second = blk.x >= pr.wgs0;
     const NearCloud &qc = pr.c[second ? 1 : 0], &pc = pr.c[second ? 0 : 1];
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     // `group` of the workgroup's query waves, and this wave's place `r` among those that share it
-    const int logw = SHARED ? pr.share[second ? 1 : 0] : 0;
+    const int logw = pr.share[second ? 1 : 0];
     const int group = wave >> logw, r = wave & ((1 << logw) - 1);
     const int qw = (blk.x - (second ? pr.wgs0 : 0)) * (WAVES >> logw) + group;
     const bool run = qw * 64 < qc.n;
-    if (!SHARED && !run) return;
-    __shared__ unsigned sbest[SHARED ? WAVES : 1][64];
-    __shared__ int sidx[SHARED ? WAVES : 1][64];
-    __shared__ int stie[SHARED ? WAVES : 1][64];
+    __shared__ unsigned sbest[WAVES][64];
+    __shared__ int sidx[WAVES][64];
+    __shared__ int stie[WAVES][64];
     const float inf = __builtin_inff();
-    if (SHARED) {
-        if (r == 0) {
-            sbest[group][lane] = __float_as_uint(inf);
-            sidx[group][lane] = 0x7fffffff;
-            stie[group][lane] = 0;
-        }
-        __syncthreads();
+    if (r == 0) {
+        sbest[group][lane] = __float_as_uint(inf);
+        sidx[group][lane] = 0x7fffffff;
+        stie[group][lane] = 0;
     }
+    __syncthreads();
     // the wave's share of a super-block's blocks
     unsigned long long share = ~0ull;
-    if (SHARED && logw == 2) share = 0x1111111111111111ull << r;
-    if (SHARED && logw == 4) share = 0x0001000100010001ull << r;
+    if (logw == 2) share = 0x1111111111111111ull << r;
+    if (logw == 4) share = 0x0001000100010001ull << r;
     const int supers_q = order_supers(qc.n), supers = order_supers(pc.n);
     const int chunks = (supers + 63) / 64;
     const int nblk = order_blocks(pc.n);
@@ -959,9 +966,7 @@ __device__ __forceinline__ void near_body(const NearParams &pr, const Blk &blk) 
     // what a lane's candidates have to come up to: its best, or that of the waves it shares with
     float bound = best;
     auto share_best = [&]() {
-        if (!SHARED) {
-            bound = best;
-        } else if (live) {
+        if (live) {
             atomicMin(&sbest[group][lane], __float_as_uint(best));
             bound = fminf(best, __uint_as_float(sbest[group][lane]));
         }
@@ -1037,7 +1042,7 @@ __device__ __forceinline__ void near_body(const NearParams &pr, const Blk &blk) 
                     s = todo ? c * 64 + (int)__builtin_ctzll(todo) : -1;
                     if (s >= 0) ahead = lane_box(pbox + (size_t)s * OBOX, lane);
                     const float l = box_box(Q, bx);
-                    if (SHARED) share_best();
+                    share_best();
                     far = wave_max(bound);
                     if (pass == 0) far = fminf(far, near);
                     unsigned long long in =
@@ -1062,11 +1067,9 @@ __device__ __forceinline__ void near_body(const NearParams &pr, const Blk &blk) 
             }
         }
     }
-    if (SHARED) {
-        share_best();
-        __syncthreads();
-        bound = live ? __uint_as_float(sbest[group][lane]) : -1.f;
-    }
+    share_best();
+    __syncthreads();
+    bound = live ? __uint_as_float(sbest[group][lane]) : -1.f;
     // the winning sub-tile again, for the smallest original index at the minimum
     bool finite = live && best < inf && best == bound;
     int found = sub < 0 ? ~sub : 0x7fffffff;
@@ -1121,26 +1124,20 @@ __device__ __forceinline__ void near_body(const NearParams &pr, const Blk &blk) 
         for (int off = 32; off > 0; off >>= 1) mine = min(mine, __shfl_xor(mine, off, 64));
         if (lane == l) found = mine;
     }
-    if (SHARED) {
-        // (also met by another wave: a tie between the waves)
-        if (finite && (atomicMin(&sidx[group][lane], found) != 0x7fffffff || tie))
-            stie[group][lane] = 1;
-        __syncthreads();
-        ties = r == 0 ? (unsigned)__popcll(__ballot(stie[group][lane])) : 0u;
-        found = sidx[group][lane];
-        best = bound;
-        finite = live && bound < inf;
-    }
-    near_finish(pr, blk, qc, pc, lane, r == 0, blk.x == 0 && t == 0 && wave == 0, q, best, found, finite,
-                ties);
+    // (also met by another wave: a tie between the waves)
+    if (finite && (atomicMin(&sidx[group][lane], found) != 0x7fffffff || tie))
+        stie[group][lane] = 1;
+    __syncthreads();
+    ties = r == 0 ? (unsigned)__popcll(__ballot(stie[group][lane])) : 0u;
+    found = sidx[group][lane];
+    best = bound;
+    finite = live && bound < inf;
+    near_finish(pr, blk, qc, pc, lane, r == 0, blk.x == 0 && t == 0 && wave == 0, q, best, found,
+                finite, ties);
 }
 
-// The same search with its blocks screened on the matrix cores: two instructions give the 32 x 64
-// screened distances of a block, of which each query keeps the least of every sub-tile; the two
-// sub-tiles that may hold its smallest canonical distance are read again at the end.  3,650 vector
-// instructions per wave in place of 6,500 (100 frames of 65,536 x 65,536, both directions: 1.22 ms
-// against 1.72 ms), now bound by the waits of six waves per SIMD as much as by vector issue.
-__device__ __forceinline__ void near_screened_body(const NearParams &pr, const Blk &blk) {
+// The search of waves that have their queries to themselves, blocks screened on the matrix cores.
+__device__ __forceinline__ void near_body(const NearParams &pr, const Blk &blk) {
     const int t = blk.y;
     const int lane = threadIdx.x;
     const bool second = blk.x >= pr.wgs0;
@@ -1256,19 +1253,6 @@ __device__ __forceinline__ void near_screened_body(const NearParams &pr, const B
         }
         meet(e, i);
     };
-    // all points of a block, one after the other
-    auto evaluate = [&](int b) {
-        scalar_f4 p = (scalar_f4)(uintptr_t)(P + (size_t)b * OB);
-#pragma unroll 1
-        for (int g = 0; g < OB; g += 4) {
-            nfloat4 v[4];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) v[j] = p[g + j];
-#pragma unroll
-            for (int j = 0; j < 4; ++j)
-                meet(canon_gap(q.x - v[j].x, q.y - v[j].y, q.z - v[j].z), __float_as_int(v[j].w));
-        }
-    };
     bool screened = false;
     unsigned long long again = 0;
     if (__ballot(live)) {
@@ -1301,7 +1285,12 @@ __device__ __forceinline__ void near_screened_body(const NearParams &pr, const B
                 if (screened) screen(seed);
             }
         }
-        auto limit = [&](float d) { return __builtin_fmaf(NEAR_UP, d, 2.f * slack); };
+        // screened values up to this one may be of a point at the canonical distance d or less
+        auto limit = [&](float d) {
+            const float qq = slack * (1.f / (3.f * NEAR_ERR));
+            const float e = 12.f * qq + 8.f * __builtin_sqrtf(qq * d) + 3.f * d;
+            return __builtin_fmaf(e, 0x1p-18f, d + slack);
+        };
         if (screened) {
             bound = live ? NEAR_UP * __uint_as_float(m1) : -1.f;
             // first the blocks as near to the queries' box as the seed, which mostly hold the
@@ -1356,10 +1345,18 @@ __device__ __forceinline__ void near_screened_body(const NearParams &pr, const B
             again = __ballot(live && (!known || __uint_as_float(m3) <= limit(best)));
         }
         // More sub-tiles than that for some queries, or values that may have overflowed: every point
-        // again whose box is no further than the best so far, for those queries one by one with a
-        // point per lane, or for many of them for all at once.
-        if (!screened || __popcll(again) > NEAR_FEW) {
-            again = 0;
+        // again whose box is no further than the best so far, for a few queries one by one with a
+        // point per lane, for more of them for all at once.
+        if (!screened || __popcll(again) > NEAR_FEW + nblk / 128) {
+            float least_d = inf;
+            int at = 0;
+            bool twice = false;
+            auto keep = [&](float d, int where) {
+                twice = d < least_d ? false : (twice || d == least_d);
+                at = d < least_d ? where : at;
+                least_d = fminf(least_d, d);
+                best = fminf(best, d);
+            };
             for (int c = 0; c < chunks; ++c) {
                 const int g = c * 64 + lane;
                 float far = wave_max(live ? best : -1.f);
@@ -1380,13 +1377,36 @@ __device__ __forceinline__ void near_screened_body(const NearParams &pr, const B
                         in &= in - 1;
                         const float e = point_box(q.x, q.y, q.z, box_of_lane(bx, k));
                         if (!__ballot(live && !(e > best))) continue;
-                        if (one >> k & 1)
-                            meet(e, __builtin_amdgcn_readlane(least, k));
-                        else
-                            evaluate(s * OSUPER + k);
+                        if (one >> k & 1) {
+                            keep(e, ~__builtin_amdgcn_readlane(least, k));
+                            continue;
+                        }
+                        scalar_f4 p = (scalar_f4)(uintptr_t)(P + (size_t)(s * OSUPER + k) * OB);
+#pragma unroll 1
+                        for (int h = 0; h < OB / OSUB; ++h) {
+                            float m = inf;
+#pragma unroll
+                            for (int j0 = 0; j0 < OSUB; j0 += OLOAD) {
+                                nfloat4 v[OLOAD];
+#pragma unroll
+                                for (int j = 0; j < OLOAD; ++j) v[j] = p[h * OSUB + j0 + j];
+                                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                                for (int j = 0; j < OLOAD; ++j)
+                                    m = fminf(m, canon_gap(q.x - v[j].x, q.y - v[j].y,
+                                                           q.z - v[j].z));
+                                __builtin_amdgcn_sched_barrier(0);
+                            }
+                            keep(m, (s * OSUPER + k) * (OB / OSUB) + h);
+                        }
                     }
                 }
             }
+            found = 0x7fffffff;
+            best = inf;
+            tie = false;
+            if (live && least_d < inf) refine(at);
+            again = __ballot(live && least_d < inf && twice);
         }
     }
     while (again) {
@@ -1440,16 +1460,12 @@ __device__ __forceinline__ void near_screened_body(const NearParams &pr, const B
                 (unsigned)__popcll(__ballot(finite && tie)));
 }
 
-__global__ __launch_bounds__(NEAR_THREADS, 8) void k_near(NearParams p) {
-    near_body<false>(p, grid_blk_xcd());
-}
-
-__global__ __launch_bounds__(SCREEN_THREADS, SCREEN_WAVES) void k_near_screened(NearParams p) {
-    near_screened_body(p, grid_blk_xcd());
+__global__ __launch_bounds__(NEAR_THREADS, NEAR_WAVES) void k_near(NearParams p) {
+    near_body(p, grid_blk_xcd());
 }
 
 __global__ __launch_bounds__(NEAR_SHARED_THREADS, 8) void k_near_shared(NearParams p) {
-    near_body<true>(p, grid_blk_xcd());
+    near_shared_body(p, grid_blk_xcd());
 }
 
 // about two points per cell
@@ -1516,16 +1532,6 @@ size_t ordered_scratch_bytes(int T, int Na, int Nb) {
     return ar.off;
 }
 
-// Whether k_near_screened takes the calls whose query waves fill the chip.  It has the longer wait for
-// a wave on a jump of the curve, which grows with the cloud and shows where few frames run beside it:
-// one to four frames of 262,144 points take 572 to 836 us with it against 288 to 625, four of 65,536
-// 148 against 190 and 100 of them 1,499 against 2,002 (ordering included).  And with few queries against
-// dense targets the slack leaves too many sub-tiles: 100 frames of 65,536 x 8,192 points take 1,008 us
-// against 956, of 65,536 x 20,000 1,139 against 1,232.
-bool near_screens(int Na, int Nb, bool two) {
-    return std::max(Na, Nb) <= 65536 && Nb <= 4L * Na && (!two || Na <= 4L * Nb);
-}
-
 void launch_ordered(const float *a, int Na, const float *b, int Nb, int T, int32_t *idx_a,
                     float *dist_a, int32_t *idx_b, float *dist_b, char *scratch,
                     unsigned long long *stats, dc_ctx *prof, hipStream_t s) {
@@ -1572,13 +1578,13 @@ void launch_ordered(const float *a, int Na, const float *b, int Nb, int T, int32
     for (int k = 0; k < 2; ++k) {
         waves[k] = order_npad(op.c[k].n) / 64;
         const long all = waves[k] * T;
-        np.share[k] = all * 4 > NEAR_FULL ? 0 : (all * 16 > NEAR_FULL ? 2 : 4);
+        const bool few = op.c[k ? 0 : 1].n <= NEAR_FEW_TARGETS;
+        np.share[k] = all < NEAR_SHARE16 ? 4 : (all <= NEAR_SHARE4 && !few ? 2 : 0);
         shared |= np.share[k] > 0 && (k == 0 || idx_b);
     }
     np.both = idx_b != nullptr;
     np.pad = 0;
-    const bool screened = !shared && near_screens(Na, Nb, idx_b != nullptr);
-    const int per = (shared ? NEAR_SHARED_THREADS : screened ? SCREEN_THREADS : NEAR_THREADS) / 64;
+    const int per = (shared ? NEAR_SHARED_THREADS : NEAR_THREADS) / 64;
     long wgs = 0;
     for (int k = 0; k < (idx_b ? 2 : 1); ++k) {
         const int groups = shared ? per >> np.share[k] : per;
@@ -1588,8 +1594,6 @@ void launch_ordered(const float *a, int Na, const float *b, int Nb, int T, int32
     ProfScope ps(prof, 0, s);
     if (shared)
         dispatch(KT_NEAR_SHARED, k_near_shared, dim3((unsigned)wgs, T), NEAR_SHARED_THREADS, np, s);
-    else if (screened)
-        dispatch(KT_NEAR_SCREENED, k_near_screened, dim3((unsigned)wgs, T), SCREEN_THREADS, np, s);
     else
         dispatch(KT_NEAR, k_near, dim3((unsigned)wgs, T), NEAR_THREADS, np, s);
 }
@@ -1600,11 +1604,9 @@ void register_ordered_kernels(BatchedKernel *table) {
     table[KT_ORDER_SCAN] = batched_kernel<OrderParams, order_scan_body, ORD_THREADS, 512>();
     table[KT_ORDER_DEAL] = batched_kernel<OrderParams, order_deal_body, OC_THREADS, 1024>();
     table[KT_ORDER_BOX] = batched_kernel<OrderParams, order_box_body, OC_THREADS, 1024>();
-    table[KT_NEAR] = batched_kernel<NearParams, near_body<false>, NEAR_THREADS, 2048, 8>();
-    table[KT_NEAR_SCREENED] =
-        batched_kernel<NearParams, near_screened_body, SCREEN_THREADS, 8192, SCREEN_WAVES>();
+    table[KT_NEAR] = batched_kernel<NearParams, near_body, NEAR_THREADS, 8192, NEAR_WAVES>();
     table[KT_NEAR_SHARED] =
-        batched_kernel<NearParams, near_body<true>, NEAR_SHARED_THREADS, 512, 8>();
+        batched_kernel<NearParams, near_shared_body, NEAR_SHARED_THREADS, 512, 8>();
 }
 
 }  // namespace dc

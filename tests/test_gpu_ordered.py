@@ -33,7 +33,7 @@ def _check(p, A, B, two=True):
 
 # points around a block (32), a query wave (64), a super-block (2,048), the largest cloud of one
 # workgroup (16,384) and a part of a larger one; frames that share query waves between 16, 4 and 1
-# waves (the chip holds 8,192: 16 below 512 query waves on a side, 4 below 2,048)
+# waves (16 below 512 query waves on a side, 4 up to 1,024 among more than 16,384 targets)
 @pytest.mark.parametrize("T,Na,Nb", [
     (1, 64, 64), (2, 65, 127), (1, 257, 2047), (1, 2049, 4095), (12, 2112, 2100), (40, 3333, 3400),
     (1, 512, 20000), (3, 9000, 1500), (1, 16384, 16384), (1, 16385, 16383), (2, 33000, 24577),

@@ -857,7 +857,7 @@ constexpr float NEAR_SAFE = 1e30f;  // |q'|^2 and v up to which nothing overflow
 // sub-tiles remain for many of the wave's queries: then the blocks in reach are evaluated once more for
 // all of them, or the queries searched one by one where those are few.  Both are a wait for one wave
 // that shows where few frames run beside it: a query takes about 4 us, a sweep of the blocks as long as
-// the tests of their boxes, so the line lies at NEAR_FEW and one query more per 128 blocks.  Two frames
+// the tests of their boxes, so the line lies at NEAR_FEW and one query more per 256 blocks.  Two frames
 // of 131,072 points take 181 us with it, 268 us with three queries at any size; one frame of 262,144
 // points 264 and 302 us (ordering included, both directions).
 constexpr int NEAR_FEW = 3;
@@ -1347,7 +1347,7 @@ __device__ __forceinline__ void near_body(const NearParams &pr, const Blk &blk) 
         // More sub-tiles than that for some queries, or values that may have overflowed: every point
         // again whose box is no further than the best so far, for a few queries one by one with a
         // point per lane, for more of them for all at once.
-        if (!screened || __popcll(again) > NEAR_FEW + nblk / 128) {
+        if (!screened || __popcll(again) > NEAR_FEW + nblk / 256) {
             float least_d = inf;
             int at = 0;
             bool twice = false;

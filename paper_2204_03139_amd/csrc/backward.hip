@@ -634,7 +634,9 @@ void launch_chamfer_bwd(const double *grad_loss, const float *a, const float *b,
     ar.cap = chamfer_bwd_scratch_bytes(T, Na, Nb, grad_b != nullptr);
     // the a side groups the b points (when beta != 0), the b side the a points
     const long items_a = beta != 0.0 ? Nb : 0;
-    const bool group_a = grouped_pays(items_a), group_b = grad_b && grouped_pays(Na);
+    // (with nothing to group, the path of the sort only has its last kernel: 100 x 65,536 rows take 73 us
+    // in it, 113 us in the grouped one)
+    const bool group_a = items_a > 0 && grouped_pays(items_a), group_b = grad_b && grouped_pays(Na);
     if (group_a || group_b) {
         GroupChamferParams gp;
         gp.grad_loss = grad_loss;

@@ -7,7 +7,10 @@ One step = the whole path over one batch of synthetic input, inputs resident in 
 for every frame of the 100-frame, 100x100-grid, 65,536 x 65,536-point trajectory workload.
 value = sum over frames of Na*Nb point pairs / seconds per step (whole job, one GPU).
 
-Prints ONE JSON line.  The roofline object refers to the all-pairs kernel (its device time is
+Every pair of the frames counts as done, also the ones that the search rules out by bounding boxes
+instead of evaluating.
+
+Prints ONE JSON line.  The roofline object refers to the search kernel (its device time is
 measured with HIP events on the stream it runs on, inside the timed region); the cpu_baseline
 object times the CPU oracle on a bounded sample of the same workload on this host's cores.
 """
@@ -26,18 +29,18 @@ METRIC = "fwd+bwd Chamfer point-pairs/s; p50/p99 request latency; BF16-MFMA vs F
 FP32_VECTOR_PEAK_TFLOPS = 157.3   # MI355X published fp32 vector peak
 BF16_MFMA_PEAK_TFLOPS = 2500.0    # MI355X published dense bf16 matrix peak
 FLOPS_PER_PAIR = 8                # 3 sub, 3 mul, 2 add: one squared distance (the algorithmic unit)
-MFMA_FLOPS_PER_PAIR = 64          # what the screen's K=32 bf16 contraction executes per pair
 CUS, SIMDS_PER_CU, PEAK_CLOCK_HZ = 256, 4, 2.4e9
-# VALU-issue ceiling of the screen's design: per 16x16 result tile (256 pairs) one MFMA issue plus
-# four v_min3 (two values folded per instruction and direction), 4 cycles each per wave64 on a SIMD
-SCREEN_ISSUE_CEILING = CUS * SIMDS_PER_CU * PEAK_CLOCK_HZ / (5 * 4) * 256
-# HBM bytes of one k_screen<true> launch on this workload, from rocprofv3 FETCH_SIZE / WRITE_SIZE
-# scaled by a plain-copy calibration (profiles/k_screen_grid100_65536pts_100frames_counters.md);
-# valid only for the machine code they were measured on (sha256 of the kernel's bytes in the
-# built library's gfx950 code object).
-SCREEN_SYMBOL = "_ZN2dc12_GLOBAL__N_18k_screenILb1EEEvNS0_12ScreenParamsE"
-SCREEN_TRAFFIC = dict(code_sha256="2b2d09a4bc2301a1a06e3d30f06b82e43131df2b13699fd1d503161ed3a412ec",
-                      bytes=739720 * 1024 * 2 + 1843269 * 1024)
+# wave64 vector instructions the chip can issue: one per two cycles and SIMD (an add or an fma; the
+# minimum family takes four)
+VECTOR_ISSUE_PEAK = CUS * SIMDS_PER_CU * PEAK_CLOCK_HZ / 2
+# Counters of one k_near launch on the 100-frame workload, both directions, from rocprofv3 (SQ_INSTS_VALU,
+# SQ_INSTS_MFMA; FETCH_SIZE and WRITE_SIZE scaled by a plain-copy calibration;
+# profiles/k_near_grid100_65536pts_100frames_counters.md); valid only for the machine code they were
+# taken on (sha256 of the kernel's bytes in the built library's gfx950 code object).
+NEAR_SYMBOL = "_ZN2dc12_GLOBAL__N_16k_nearENS0_10NearParamsE"
+NEAR_COUNTERS = dict(code_sha256="d5daaaec35d73b24e914ae6acdebd4b1609fa514a95da2f9def0ca6c7603a0e6", vector_insts=693802000, mfma_insts=8187720,
+                     bytes=122843 * 1024 * 2 + 136195 * 1024)
+MFMA_FLOPS = 2 * 32 * 32 * 16     # of one v_mfma_f32_32x32x16_bf16
 LIB = os.path.join(os.path.dirname(os.path.abspath(__file__)), "paper_2204_03139_amd",
                    "libdiffcloud.so")
 
@@ -83,14 +86,15 @@ def kernel_code_sha256(lib_path: str, symbol: str):
                     return hashlib.sha256(elf[off:off + size]).hexdigest(), size
 
 
-def _screen_traffic():
+def _near_counters(T, Na, Nb):
+    """(the counters that hold for the built kernel on this workload or None, the built kernel's sha256)"""
     try:
-        h = kernel_code_sha256(LIB, SCREEN_SYMBOL)
+        h = kernel_code_sha256(LIB, NEAR_SYMBOL)
     except (OSError, ValueError, struct.error):
-        return None
-    if h is None or SCREEN_TRAFFIC["code_sha256"] is None:
-        return None
-    return SCREEN_TRAFFIC["bytes"] if h[0] == SCREEN_TRAFFIC["code_sha256"] else None
+        h = None
+    code = h[0] if h else None
+    same = (T, Na, Nb) == (100, 65536, 65536) and code == NEAR_COUNTERS["code_sha256"]
+    return (NEAR_COUNTERS if same else None), code
 
 
 def _args():
@@ -458,9 +462,7 @@ def main():
             paths[name] = dict(error=str(e))
             continue
         nn_ms, nn_n = kt["all_pairs"]
-        # the all-pairs launches of one step cover every pair of every frame once: the fp32 path
-        # launches its one-pass search (and its column merge) once, the screen once for both
-        # directions
+        # one launch of the search covers both directions of every frame
         per_launch_pairs = pairs * a.steps / max(nn_n, 1)
         avg = nn_ms / max(nn_n, 1)
         paths[name] = dict(pairs_per_s=pairs / (ms * 1e-3), ms_per_step=ms,
@@ -476,58 +478,37 @@ def main():
         sys.exit(1)
     best = max(ok, key=lambda k: ok[k]["pairs_per_s"])
     bp = ok[best]
-    # Both all-pairs kernels are bound by vector-ALU issue (the screen's minimum reductions; the
-    # exact search's distance arithmetic), so the roofline is the fp32 vector peak against the
-    # algorithmic 8 flops per pair.  The screen's matrix-core use is reported beside it.
-    pps = bp["all_pairs_pairs_per_s"]
-    achieved = FLOPS_PER_PAIR * pps / 1e12
-    roof = dict(bound="alu", achieved=achieved, peak=FP32_VECTOR_PEAK_TFLOPS, unit="TFLOP/s",
-                frac=achieved / FP32_VECTOR_PEAK_TFLOPS, flops_per_pair=FLOPS_PER_PAIR)
-    if best == "bf16_refine":
-        mf = MFMA_FLOPS_PER_PAIR * pps / 1e12
-        code = kernel_code_sha256(LIB, SCREEN_SYMBOL)
-        roof.update(traffic=_screen_traffic(),
-                    traffic_key=dict(kernel_code_sha256=code[0] if code else None,
-                                     counters_taken_on=SCREEN_TRAFFIC["code_sha256"]),
-                    kernel="k_screen<true>: bf16 matrix-core screen, both directions in one "
-                           "launch over all frames",
-                    launch_ms=bp["all_pairs_avg_launch_ms"],
-                    binding_unit=dict(
-                        unit="vector issue (one MFMA issue + four v_min3 per 256 pairs per SIMD, "
-                             "4 cycles each)",
-                        ceiling_pairs_per_s=SCREEN_ISSUE_CEILING, clock_ghz=PEAK_CLOCK_HZ / 1e9,
-                        frac=pps / SCREEN_ISSUE_CEILING),
-                    issue_ceiling_pairs_per_s=SCREEN_ISSUE_CEILING,
-                    frac_of_issue_ceiling=pps / SCREEN_ISSUE_CEILING,
-                    mfma=dict(executed_flops_per_pair=MFMA_FLOPS_PER_PAIR, achieved=mf,
-                              peak=BF16_MFMA_PEAK_TFLOPS, unit="TFLOP/s",
+    # Either precision is served by the same search where the clouds are large enough to order (its
+    # result is the exhaustive fp32 search's), so the roofline is that kernel's: the vector instructions
+    # it issues against what the SIMDs can issue.  Its matrix-core use is reported beside it.
+    counters, code = _near_counters(T, Na, Nb)
+    roof = dict(bound="alu", achieved=None, peak=VECTOR_ISSUE_PEAK / 1e9, unit="Ginst/s (wave64)",
+                frac=None, traffic=None, launch_ms=bp["all_pairs_avg_launch_ms"],
+                pairs_per_s=bp["all_pairs_pairs_per_s"],
+                kernel="k_near: nearest neighbours over ordered clouds, both directions of all frames "
+                       "in one launch; blocks within reach screened on the matrix cores",
+                counters_key=dict(kernel_code_sha256=code,
+                                  counters_taken_on=NEAR_COUNTERS["code_sha256"]))
+    if counters and bp["all_pairs_avg_launch_ms"]:
+        sec = bp["all_pairs_avg_launch_ms"] * 1e-3
+        rate, mf = counters["vector_insts"] / sec, counters["mfma_insts"] * MFMA_FLOPS / sec / 1e12
+        roof.update(achieved=rate / 1e9, frac=rate / VECTOR_ISSUE_PEAK, traffic=counters["bytes"],
+                    traffic_tb_per_s=counters["bytes"] / sec / 1e12,
+                    mfma=dict(achieved=mf, peak=BF16_MFMA_PEAK_TFLOPS, unit="TFLOP/s",
                               frac=mf / BF16_MFMA_PEAK_TFLOPS))
-        eq2 = paths.get("bf16_refine_eq2")
-        if eq2 and "error" not in eq2 and eq2.get("all_pairs_pairs_per_s"):
-            # the rows-only screen of Eq. 2 is bound by the matrix pipe: one K=32 bf16 MFMA per
-            # 256 pairs, 64 executed flops per pair against the dense bf16 peak
-            e_mf = MFMA_FLOPS_PER_PAIR * eq2["all_pairs_pairs_per_s"] / 1e12
-            roof["eq2_screen"] = dict(kernel="k_screen<false>", bound="mfma", achieved=e_mf,
-                                      peak=BF16_MFMA_PEAK_TFLOPS, unit="TFLOP/s",
-                                      frac=e_mf / BF16_MFMA_PEAK_TFLOPS,
-                                      launch_ms=eq2["all_pairs_avg_launch_ms"])
-    else:
-        roof.update(traffic=None,
-                    kernel="k_nn_bidir + k_bidir_merge: exact fp32 search, both directions in one "
-                           "pass over all frames",
-                    launch_ms=bp["all_pairs_avg_launch_ms"])
     # the pair roofline: fp32 vector peak / 8 flops per pair, for the whole bidirectional step
     pair_peak = FP32_VECTOR_PEAK_TFLOPS * 1e12 / FLOPS_PER_PAIR
     line = dict(
         metric=METRIC, value=bp["pairs_per_s"], unit="point-pairs/s", n_gpus=1, steps=a.steps,
         warmup=a.warmup, ms_per_step=bp["ms_per_step"], higher_is_better=True, scaling="weak",
-        vs_baseline=None, dtype="f32" if best == "fp32" else "bf16+f32", data="synthetic",
+        vs_baseline=None, dtype="bf16+f32", data="synthetic",
         config=dict(workload=w["name"], frames=T, n_sim=Na, n_obs=Nb, grid=gen.CONFIGS[a.workload]
                     .get("n"), faces=w["F"], precision=best, reduction="Eq. 1 (bidirectional mean)",
                     pairs_per_step=pairs),
         roofline=roof,
         pair_roofline=dict(peak_pairs_per_s=pair_peak, frac_of_step=bp["pairs_per_s"] / pair_peak,
-                           note="fp32 vector peak / 8 flops per pair; whole fwd+bwd step"),
+                           note="fp32 vector peak / 8 flops per pair, were every pair evaluated; "
+                                "whole fwd+bwd step"),
         paths=paths,
     )
     if not a.no_configs and a.workload == 4 and a.frames is None:

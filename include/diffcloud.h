@@ -236,9 +236,10 @@ int dc_rigid_pose_bwd(dc_ctx *ctx, const double *q, const float *p0, const int32
 
 /* Counters of the DC_PREC_BF16_REFINE searches since the context was created (read after dc_sync):
  *   queries    nearest-neighbour queries answered by the ordered or the screened search
- *   candidates candidate groups re-evaluated exactly (ordered: the 16 points around the minimum)
+ *   candidates candidate groups re-evaluated exactly (ordered: one per query, the 16 points around
+ *              its minimum)
  *   fallbacks  queries searched a second time: whose certificate failed (screen), or whose minimum
- *              was met in more than one group (ordered) */
+ *              was met more than once (ordered) */
 typedef struct dc_stats {
     uint64_t queries;
     uint64_t candidates;

@@ -1509,12 +1509,13 @@ bool order_is_small(int Na, int Nb) { return std::max(Na, Nb) <= ORD_SMALL; }
 
 // Where this search is the fastest, measured over 1 to 4,096 frames of 32 to 65,536 points (us, the
 // exact search / the bf16 screen / this one, for both directions).  64 frames of 64 x 64: 32 / 82 /
-// 26, of 1,024 x 1,024: 77 / 109 / 41, of 8,192 x 8,192: 766 / 414 / 144.  Ordering costs as much
+// 26, of 1,024 x 1,024: 77 / 109 / 37, of 8,192 x 8,192: 766 / 414 / 121.  Ordering costs as much
 // as a few hundred targets do, so a handful of points against many is left to the exact search:
-// 100 frames of 32,768 x 64: 213 / 814 / 315, of 32,768 x 512: 410 / 869 / 365; but on one or a few
-// frames the exact search leaves the chip idle: one frame of 8,192 x 128: 108 / 95 / 62.  One
+// 100 frames of 32,768 x 64: 213 / 814 / 315, of 32,768 x 512: 410 / 869 / 361; but on one or a few
+// frames the exact search leaves the chip idle: one frame of 8,192 x 128: 108 / 95 / 60.  One
 // direction: 64 frames of 256 x 256: 25 / 72 / 26, of 1,024 x 1,024: 42 / 73 / 34; few queries
 // against many targets gain least (one frame of 512 x 32,768: 66 / 260 / 81; 100: 497 / 322 / 236).
+// (The ordered search's times where it is not taken are from before its blocks were screened.)
 bool ordered_pays(int T, int Na, int Nb, bool two) {
     const int lo = std::min(Na, Nb), hi = std::max(Na, Nb);
     const bool few = (long)T * hi <= 65536;

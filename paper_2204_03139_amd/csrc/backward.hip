@@ -206,10 +206,11 @@ __global__ __launch_bounds__(BW_THREADS) void k_vertex_grad(VertexGradParams p) 
 //
 // Workgroups of 512 threads, four to a compute unit, for up to GP_WIDE items a frame, else of 1,024,
 // two to a compute unit: fewer workgroups then read the keys.  The three kernels of a backward, 512
-// against 1,024 threads: 40 frames of 8,192 points 44 / 62 us (165 us with sorts), 17 frames of
-// 30,011 x 5,003 (both gradients) 72 / 91 (198), 100 frames of 65,536 607 / 513 (697).
+// against 1,024 threads: 40 frames of 8,192 points 38 / 55 us (165 us with sorts), 17 frames of
+// 30,011 x 5,003 (both gradients) 69 / 77 (198), 24 frames of 32,768 x 20,011 76 / 91, 100 frames of
+// 65,536 538 / 452 (697).
 constexpr int GP_SMALL = 512, GP_LARGE = 1024;
-constexpr int GP_WIDE = 32768;
+constexpr int GP_WIDE = 49152;
 constexpr int GP_IBITS = 17;      // bits of an item in a listed word, below its key
 constexpr int GP_MAX = 1 << GP_IBITS;
 
@@ -220,10 +221,15 @@ static_assert(gp_cap<GP_LARGE>() <= 1 << (32 - GP_IBITS), "a key and an item sha
 
 template <int TH>
 struct GroupLds {
-    int start[gp_cap<TH>() + 4];    // first position of each key's items, over the workgroup's range
-    int cursor[gp_cap<TH>()];
-    unsigned listed[gp_cap<TH>()];
-    int item[gp_cap<TH>()];         // the items, by key and then in increasing order
+    int start[gp_cap<TH>() + 4];  // first position of each key's items, over the workgroup's range
+    union {
+        struct {
+            int cursor[gp_cap<TH>()];
+            unsigned listed[gp_cap<TH>()];
+            int item[gp_cap<TH>()];  // the items, by key and then in increasing order
+        };
+        float row[3][gp_cap<TH>()];  // in their place, what the items stand for
+    };
     int wsum[TH / 64];
     double part[TH / 64][9];
 };
@@ -262,15 +268,21 @@ __device__ __forceinline__ void each_key(const int32_t *__restrict__ keys, int n
     if ((int)threadIdx.x < n - whole) visit(whole + (int)threadIdx.x, keys[whole + threadIdx.x]);
 }
 
+struct Row3 {
+    float v[3];
+};
+
 // For every key in [k0, k0 + nk): `own(key)` reads what the key itself needs, `each(own, item, on, sum)`
-// adds an item to its sum (nothing unless `on`), `put(key, own, sum)` takes the total; a thread has U
-// keys in hand at a time and G lanes share one.  A round lists as many keys as fit CAP items; a key
-// with more is summed by the whole workgroup, straight from the keys, each thread its every
-// TH-th item.
-template <int TH, int M, int U, class Own, class Each, class Put>
+// adds what `fetch(item)` gives to its sum (nothing unless `on`), `put(key, own, sum)` takes the total; G
+// lanes share a key.  A round lists as many keys as fit CAP items; a key with more is summed by the whole
+// workgroup, straight from the keys, each thread its every TH-th item.  Rows of three floats (STAGE) are
+// fetched into LDS before the sums, by all lanes and four at a time: fetched by the lanes of a key, most
+// of a wave's lanes wait for its longest key, and two keys in hand to fill the waits spilled registers
+// (Chamfer backward of 100 x 65,536 points 256 -> 191 us, of 40 x 8,192 18.2 -> 12.7 us).
+template <int TH, int M, bool STAGE, class Own, class Fetch, class Each, class Put>
 __device__ __forceinline__ void grouped_sums(const int32_t *__restrict__ keys, int n, int k0, int nk,
-                                             int G, GroupLds<TH> &s, const Own &own, const Each &each,
-                                             const Put &put) {
+                                             int G, GroupLds<TH> &s, const Own &own, const Fetch &fetch,
+                                             const Each &each, const Put &put) {
     constexpr int CAP = gp_cap<TH>(), WAVES = TH / 64;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     for (int k = tid; k < nk; k += TH) s.cursor[k] = 0;
@@ -346,13 +358,28 @@ __device__ __forceinline__ void grouped_sums(const int32_t *__restrict__ keys, i
             }
             __syncthreads();
         }
+        if constexpr (STAGE) {
+            if (total > 0 && !giant) {
+                constexpr int PER = CAP / TH;
+                decltype(fetch(0)) f[PER];
+#pragma unroll
+                for (int u = 0; u < PER; ++u) f[u] = fetch(s.item[min(tid + u * TH, total - 1)]);
+                __syncthreads();
+#pragma unroll
+                for (int u = 0; u < PER; ++u)
+                    if (tid + u * TH < total)
+#pragma unroll
+                        for (int d = 0; d < 3; ++d) s.row[d][tid + u * TH] = f[u].v[d];
+                __syncthreads();
+            }
+        }
         if (giant) {
             const auto whole = own(k0 + kb);
             double v[M];
 #pragma unroll
             for (int m = 0; m < M; ++m) v[m] = 0.0;
 #pragma unroll 1
-            for (int i = tid; i < n; i += TH) each(whole, i, keys[i] == k0 + kb, v);
+            for (int i = tid; i < n; i += TH) each(whole, fetch(i), keys[i] == k0 + kb, v);
             team_sum(v, 64);
             if (lane == 0)
 #pragma unroll
@@ -361,45 +388,29 @@ __device__ __forceinline__ void grouped_sums(const int32_t *__restrict__ keys, i
         }
         const int per = TH / G, l = tid & (G - 1);
 #pragma unroll 1
-        for (int k = giant ? kb + tid : kb + tid / G; k < ke; k += U * per) {
-            int ku[U], e[U], hi[U];
-            double v[U][M];
-            decltype(own(0)) mine[U];
+        for (int k = giant ? kb + tid : kb + tid / G; k < ke; k += per) {
+            double v[M];
+            const auto mine = own(k0 + k);
+            const int hi = giant ? 0 : s.start[k + 1] - base;
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const bool ok = k + u * per < ke;
-                ku[u] = ok ? k + u * per : k;
-                mine[u] = own(k0 + ku[u]);
-                e[u] = s.start[ku[u]] - base + l;
-                hi[u] = ok && !giant ? s.start[ku[u] + 1] - base : 0;
-#pragma unroll
-                for (int m = 0; m < M; ++m) v[u][m] = 0.0;
-            }
+            for (int m = 0; m < M; ++m) v[m] = 0.0;
 #pragma unroll 1
-            for (;;) {  // an item of each of the U keys at a time, their loads in flight together
-                bool more = false;
+            for (int e = s.start[k] - base + l; e < hi; e += G) {
+                decltype(fetch(0)) f;
+                if constexpr (STAGE)
 #pragma unroll
-                for (int u = 0; u < U; ++u) more = more || e[u] < hi[u];
-                if (!more) break;
-                int i[U];
-#pragma unroll
-                for (int u = 0; u < U; ++u) i[u] = s.item[e[u] < hi[u] ? e[u] : 0];
-#pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    each(mine[u], i[u], e[u] < hi[u], v[u]);
-                    e[u] += G;
-                }
+                    for (int d = 0; d < 3; ++d) f.v[d] = s.row[d][e];
+                else
+                    f = fetch(s.item[e]);
+                each(mine, f, true, v);
             }
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                team_sum(v[u], G);
-                if (giant)
+            team_sum(v, G);
+            if (giant)
 #pragma unroll 1
-                    for (int w = 0; w < WAVES; ++w)
+                for (int w = 0; w < WAVES; ++w)
 #pragma unroll
-                        for (int m = 0; m < M; ++m) v[u][m] += s.part[w][m];
-                if (l == 0 && k + u * per < ke) put(k0 + ku[u], mine[u], v[u]);
-            }
+                    for (int m = 0; m < M; ++m) v[m] += s.part[w][m];
+            if (l == 0) put(k0 + k, mine, v);
         }
         __syncthreads();  // the next round lists anew
         kb = ke;
@@ -454,12 +465,13 @@ __device__ __forceinline__ void group_chamfer_body(const GroupChamferParams &pr,
         return o;
     };
     // in double (each difference of two floats is exact there) and rounded once to float, as below
-    auto each = [&](const Own &o, int j, bool on, double (&v)[3]) {
+    auto fetch = [&](int j) {
         const float *py = yt + 3 * (size_t)j;
-        const float d0 = py[0], d1 = py[1], d2 = py[2];
-        v[0] += on ? (double)o.x[0] - (double)d0 : 0.0;
-        v[1] += on ? (double)o.x[1] - (double)d1 : 0.0;
-        v[2] += on ? (double)o.x[2] - (double)d2 : 0.0;
+        return Row3{{py[0], py[1], py[2]}};
+    };
+    auto each = [](const Own &o, const Row3 &y, bool on, double (&v)[3]) {
+#pragma unroll
+        for (int d = 0; d < 3; ++d) v[d] += on ? (double)o.x[d] - (double)y.v[d] : 0.0;
     };
     auto put = [&](int i, const Own &o, double (&v)[3]) {
         float *g3 = x.gX + ((size_t)t * x.N + i) * 3;
@@ -476,8 +488,8 @@ __device__ __forceinline__ void group_chamfer_body(const GroupChamferParams &pr,
         g3[2] = r[2];
     };
     // without the mutual term there is nothing to group
-    grouped_sums<TH, 3, 2>(y.nn ? y.nn + (size_t)t * y.N : nullptr, cm != 0.0 ? y.N : 0, k0, nk, x.team,
-                       lds, own, each, put);
+    grouped_sums<TH, 3, true>(y.nn ? y.nn + (size_t)t * y.N : nullptr, cm != 0.0 ? y.N : 0, k0, nk,
+                                 x.team, lds, own, fetch, each, put);
 }
 
 template <int TH>
@@ -502,6 +514,7 @@ __device__ __forceinline__ void group_face_body(const GroupFaceParams &pr, const
     const float *bt = pr.bary + (size_t)t * pr.N * 3;
     float *ft = pr.fg + (size_t)t * pr.F * 9;
     auto own = [](int) { return 0; };
+    auto fetch = [](int i) { return i; };
     auto each = [&](int, int i, bool on, double (&v)[9]) {
         const float *g = gt + 3 * (size_t)i, *b = bt + 3 * (size_t)i;
         const float f0 = g[0], f1 = g[1], f2 = g[2], w3[3] = {b[0], b[1], b[2]};
@@ -518,8 +531,8 @@ __device__ __forceinline__ void group_face_body(const GroupFaceParams &pr, const
 #pragma unroll
         for (int m = 0; m < 9; ++m) ft[9 * (size_t)f + m] = (float)v[m];
     };
-    grouped_sums<TH, 9, 1>(pr.face_idx + (size_t)t * pr.N, pr.N, k0, min(pr.keys, pr.F - k0), pr.team, lds,
-                       own, each, put);
+    grouped_sums<TH, 9, false>(pr.face_idx + (size_t)t * pr.N, pr.N, k0, min(pr.keys, pr.F - k0),
+                                  pr.team, lds, own, fetch, each, put);
 }
 
 template <int TH>
@@ -542,18 +555,20 @@ __device__ __forceinline__ void group_vertex_body(const GroupVertexParams &pr, c
     const float *ft = pr.fg + (size_t)t * pr.F * 9;
     float *gv = pr.gverts + (size_t)t * pr.V * 3;
     auto own = [](int) { return 0; };
-    auto each = [&](int, int fc, bool on, double (&v)[3]) {  // fc = 3 f + c
+    auto fetch = [&](int fc) {  // fc = 3 f + c
         const float *p = ft + 3 * (size_t)fc;
-        const float p0 = p[0], p1 = p[1], p2 = p[2];
-        v[0] += on ? (double)p0 : 0.0;
-        v[1] += on ? (double)p1 : 0.0;
-        v[2] += on ? (double)p2 : 0.0;
+        return Row3{{p[0], p[1], p[2]}};
+    };
+    auto each = [](int, const Row3 &r, bool on, double (&v)[3]) {
+#pragma unroll
+        for (int d = 0; d < 3; ++d) v[d] += on ? (double)r.v[d] : 0.0;
     };
     auto put = [&](int v, int, double (&s)[3]) {
 #pragma unroll
         for (int d = 0; d < 3; ++d) gv[3 * (size_t)v + d] = (float)s[d];
     };
-    grouped_sums<TH, 3, 2>(pr.faces, 3 * pr.F, k0, min(pr.keys, pr.V - k0), pr.team, lds, own, each, put);
+    grouped_sums<TH, 3, true>(pr.faces, 3 * pr.F, k0, min(pr.keys, pr.V - k0), pr.team, lds, own,
+                                 fetch, each, put);
 }
 
 template <int TH>

@@ -1605,7 +1605,8 @@ void register_ordered_kernels(BatchedKernel *table) {
     table[KT_ORDER_SCAN] = batched_kernel<OrderParams, order_scan_body, ORD_THREADS, 512>();
     table[KT_ORDER_DEAL] = batched_kernel<OrderParams, order_deal_body, OC_THREADS, 1024>();
     table[KT_ORDER_BOX] = batched_kernel<OrderParams, order_box_body, OC_THREADS, 1024>();
-    table[KT_NEAR] = batched_kernel<NearParams, near_body, NEAR_THREADS, 8192, NEAR_WAVES>();
+    // (one wave per SIMD less than the direct kernel, where it would spill: 41.5 -> 39.4 us for 38 frames)
+    table[KT_NEAR] = batched_kernel<NearParams, near_body, NEAR_THREADS, 8192, NEAR_WAVES - 1>();
     table[KT_NEAR_SHARED] =
         batched_kernel<NearParams, near_shared_body, NEAR_SHARED_THREADS, 512, 8>();
 }

@@ -316,7 +316,9 @@ __device__ __forceinline__ nfloat4 padding_point() {
     return ordered_point(nan, nan, nan, -1);
 }
 
-// the box of block `b` (of `nblk`) by four lanes, eight points each; NaN points stretch nothing
+// the box of block `b` (of `nblk`) by four lanes, eight points each.  A point with a NaN coordinate is
+// left out on every axis: its distances are NaN and never win, and a box that it stretched on its other
+// axes might hold no point at all.
 __device__ __forceinline__ void block_box(const nfloat4 *pts, int b, int nblk, int tid, float *box) {
     const float inf = __builtin_inff();
     float l[3] = {inf, inf, inf}, h[3] = {-inf, -inf, -inf};
@@ -327,14 +329,14 @@ __device__ __forceinline__ void block_box(const nfloat4 *pts, int b, int nblk, i
         for (int k = 0; k < OB / 4; ++k) v[k] = pts[(size_t)b * OB + 4 * k + (tid & 3)];
 #pragma unroll
         for (int k = 0; k < OB / 4; ++k) {
-            l[0] = fminf(l[0], v[k].x);
-            l[1] = fminf(l[1], v[k].y);
-            l[2] = fminf(l[2], v[k].z);
-            h[0] = fmaxf(h[0], v[k].x);
-            h[1] = fmaxf(h[1], v[k].y);
-            h[2] = fmaxf(h[2], v[k].z);
-            if (v[k].x == v[k].x && v[k].y == v[k].y && v[k].z == v[k].z)
-                least = min(least, __float_as_int(v[k].w));
+            const bool whole = v[k].x == v[k].x && v[k].y == v[k].y && v[k].z == v[k].z;
+            l[0] = fminf(l[0], whole ? v[k].x : inf);
+            l[1] = fminf(l[1], whole ? v[k].y : inf);
+            l[2] = fminf(l[2], whole ? v[k].z : inf);
+            h[0] = fmaxf(h[0], whole ? v[k].x : -inf);
+            h[1] = fmaxf(h[1], whole ? v[k].y : -inf);
+            h[2] = fmaxf(h[2], whole ? v[k].z : -inf);
+            if (whole) least = min(least, __float_as_int(v[k].w));
         }
     }
     least = min(least, __builtin_amdgcn_update_dpp(least, least, 0xB1, 0xF, 0xF, false));
@@ -737,8 +739,8 @@ __device__ __forceinline__ Box box_of_lane(const Box &b, int l) {
     return r;
 }
 
-// whether all points of the box are the same, finite one: then the distance to the box is the
-// canonical distance to each of them, bit for bit
+// whether all points of the box are the same, finite one (a box without points is inverted): then the
+// distance to the box is the canonical distance to each of them, bit for bit
 __device__ __forceinline__ bool one_point(const Box &b) {
     bool r = true;
 #pragma unroll

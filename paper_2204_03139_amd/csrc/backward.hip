@@ -52,16 +52,17 @@ __device__ __forceinline__ void chamfer_bwd_body(const ChamferBwdParams &pr, con
     // points share this neighbour
     const double x0 = xt[3 * (size_t)i], x1 = xt[3 * (size_t)i + 1], x2 = xt[3 * (size_t)i + 2];
     double g0 = 0.0, g1 = 0.0, g2 = 0.0;
-    // the own-neighbour term exists only when cs != 0 (nn_x may be NULL otherwise: the b side of
-    // the unidirectional loss has no neighbour indices)
-    const int jn = (cs != 0.0) ? nn_x[(size_t)t * Nx + i] : -1;
+    // the own-neighbour term exists only when cself != 0 (nn_x may be NULL otherwise: the b side of
+    // the unidirectional loss has no neighbour indices), whatever the upstream gradient: 0 NaN is
+    // not 0
+    const int jn = (cself != 0.0 && cs != 0.0) ? nn_x[(size_t)t * Nx + i] : -1;
     if ((unsigned)jn < (unsigned)Ny) {  // indices outside [0, Ny) contribute nothing
         const int j = jn;
         g0 = cs * (x0 - (double)yt[3 * (size_t)j]);
         g1 = cs * (x1 - (double)yt[3 * (size_t)j + 1]);
         g2 = cs * (x2 - (double)yt[3 * (size_t)j + 2]);
     }
-    if (cm != 0.0) {
+    if (cmutual != 0.0 && cm != 0.0) {  // (the segments are there only when cmutual != 0)
         const int32_t *vs = yvals_sorted + (size_t)t * Ny;
         const int32_t *st = ystart + (size_t)t * (Nx + 1);
         const int lo = st[i], hi = st[i + 1];
@@ -445,7 +446,10 @@ __device__ __forceinline__ void group_chamfer_body(const GroupChamferParams &pr,
     if (k0 >= x.N) return;
     const int nk = min(x.keys, x.N - k0);
     const double g = pr.grad_loss[t] * (pr.frame_w ? (double)pr.frame_w[t] : 1.0);
-    const double cs = (b ? pr.cself[1] : pr.cself[0]) * g, cm = (b ? pr.cself[0] : pr.cself[1]) * g;
+    const double cself = b ? pr.cself[1] : pr.cself[0], cmutual = b ? pr.cself[0] : pr.cself[1];
+    const double cs = cself * g, cm = cmutual * g;
+    // a side without the term has no indices for it, whatever the upstream gradient (0 NaN is not 0)
+    const bool self = cself != 0.0 && cs != 0.0, mutual = cmutual != 0.0 && cm != 0.0;
     const float *xt = x.X + (size_t)t * x.N * 3;
     const float *yt = y.X + (size_t)t * y.N * 3;
     struct Own {
@@ -454,7 +458,7 @@ __device__ __forceinline__ void group_chamfer_body(const GroupChamferParams &pr,
     };
     auto own = [&](int i) {
         Own o;
-        const int j = cs != 0.0 ? x.nn[(size_t)t * x.N + i] : -1;
+        const int j = self ? x.nn[(size_t)t * x.N + i] : -1;
         o.near = (unsigned)j < (unsigned)y.N;  // indices outside [0, Ny) contribute nothing
         const float *py = yt + 3 * (size_t)(o.near ? j : 0);
 #pragma unroll
@@ -480,7 +484,7 @@ __device__ __forceinline__ void group_chamfer_body(const GroupChamferParams &pr,
         for (int d = 0; d < 3; ++d) {
             double s = 0.0;
             if (o.near) s = cs * ((double)o.x[d] - (double)o.y[d]);
-            if (cm != 0.0) s += cm * v[d];
+            if (mutual) s += cm * v[d];
             r[d] = (float)s;
         }
         g3[0] = r[0];
@@ -488,7 +492,7 @@ __device__ __forceinline__ void group_chamfer_body(const GroupChamferParams &pr,
         g3[2] = r[2];
     };
     // without the mutual term there is nothing to group
-    grouped_sums<TH, 3, true>(y.nn ? y.nn + (size_t)t * y.N : nullptr, cm != 0.0 ? y.N : 0, k0, nk,
+    grouped_sums<TH, 3, true>(y.nn ? y.nn + (size_t)t * y.N : nullptr, mutual ? y.N : 0, k0, nk,
                                  x.team, lds, own, fetch, each, put);
 }
 

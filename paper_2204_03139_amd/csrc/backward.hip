@@ -405,8 +405,9 @@ __device__ __forceinline__ void grouped_sums(const int32_t *__restrict__ keys, i
                     f = fetch(s.item[e]);
                 each(mine, f, true, v);
             }
-            team_sum(v, G);
-            if (giant)
+            if (!giant)
+                team_sum(v, G);
+            else  // by lane 0 alone, from the waves' sums
 #pragma unroll 1
                 for (int w = 0; w < WAVES; ++w)
 #pragma unroll

@@ -44,7 +44,7 @@ bool forced_alloc_failure(dc_ctx *ctx) {
     return true;
 }
 
-int dev_alloc_raw(dc_ctx *ctx, void **p, size_t bytes) {
+int dev_alloc(dc_ctx *ctx, void **p, size_t bytes) {
     *p = nullptr;
     if (bytes == 0) return DC_OK;
     int rc = budget_take(ctx, bytes);
@@ -60,16 +60,6 @@ int dev_alloc_raw(dc_ctx *ctx, void **p, size_t bytes) {
     return DC_OK;
 }
 
-int dev_alloc(dc_ctx *ctx, void **p, size_t bytes) {
-    *p = nullptr;
-    if (bytes == 0) return DC_OK;
-    if (forced_alloc_failure(ctx)) {
-        set_error("device allocation of " + std::to_string(bytes) + " bytes failed (forced)");
-        return DC_ERR_NOMEM;
-    }
-    return dev_alloc_raw(ctx, p, bytes);
-}
-
 void dev_free(dc_ctx *ctx, void *p, size_t bytes) {
     if (!p) return;
     (void)hipFree(p);
@@ -82,12 +72,33 @@ int arena_reserve(dc_ctx *ctx, size_t bytes, hipStream_t s) {
     Arena &a = ctx->arena;
     a.reset();
     if (bytes <= a.cap) return DC_OK;
+    const size_t want = (bytes + (size_t(1) << 20) - 1) & ~((size_t(1) << 20) - 1);
+    // A size that cannot be had leaves the buffer as it is: a call that then makes do with less scratch
+    // finds it there, and neither waits nor allocates on each call.
+    {
+        std::lock_guard<std::mutex> g(ctx->budget_mu);
+        const size_t room = ctx->budget - ctx->held + a.cap;
+        if (want > room) {
+            set_error("HBM budget exceeded: need " + std::to_string(want) + " bytes, " +
+                      std::to_string(room) + " free");
+            return DC_ERR_BUDGET;
+        }
+    }
+    if (forced_alloc_failure(ctx)) {
+        set_error("device allocation of " + std::to_string(want) + " bytes failed (forced)");
+        return DC_ERR_NOMEM;
+    }
+    size_t left = 0, all = 0;
+    DC_HIP(hipMemGetInfo(&left, &all));
+    if (want > left + a.cap) {
+        set_error("device allocation of " + std::to_string(want) + " bytes failed");
+        return DC_ERR_NOMEM;
+    }
     // the old buffer may still be read by queued work: wait for the device before freeing it
     DC_HIP(hipDeviceSynchronize());
     dev_free(ctx, a.base, a.cap);
     a.base = nullptr;
     a.cap = 0;
-    const size_t want = (bytes + (size_t(1) << 20) - 1) & ~((size_t(1) << 20) - 1);
     void *p = nullptr;
     int rc = dev_alloc(ctx, &p, want);
     if (rc != DC_OK) return rc;
@@ -492,8 +503,8 @@ int dc_chamfer_fwd(dc_ctx *ctx, const float *a, const float *b, int T, int Na, i
     Search search = plan_search(T, Na, Nb, precision, idx_b != nullptr, true);
     size_t need = search_scratch_bytes(search, T, Na, Nb);
     rc = arena_reserve(ctx, need, static_cast<hipStream_t>(stream));
-    if (rc == DC_ERR_BUDGET && search == Search::ordered) {
-        // the exact search may need less than the ordered clouds
+    if ((rc == DC_ERR_BUDGET || rc == DC_ERR_NOMEM) && search == Search::ordered) {
+        // the other searches may need less than the ordered clouds
         search = plan_search(T, Na, Nb, precision, idx_b != nullptr, false);
         need = search_scratch_bytes(search, T, Na, Nb);
         clear_error();

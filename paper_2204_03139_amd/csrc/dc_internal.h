@@ -93,12 +93,11 @@ constexpr size_t STATS_BYTES = sizeof(unsigned long long) * STATS_SLOTS * STATS_
 constexpr size_t CTX_WORDS_BYTES = sizeof(unsigned) * 4 + STATS_BYTES;
 // test hook: true (and one fewer pending) when the next allocation is to fail
 bool forced_alloc_failure(dc_ctx *ctx);
-// device allocation counted against the budget; dev_alloc honours the test hook, dev_alloc_raw
-// does not (its caller has consulted the hook for the allocation it serves)
+// device allocation counted against the budget (its caller has consulted the test hook)
 int dev_alloc(dc_ctx *ctx, void **p, size_t bytes);
-int dev_alloc_raw(dc_ctx *ctx, void **p, size_t bytes);
 void dev_free(dc_ctx *ctx, void *p, size_t bytes);
-// Make sure the direct-call arena holds at least `bytes` and reset its offset.  When the previous
+// Make sure the direct-call arena holds at least `bytes` and reset its offset; where the budget or the
+// device has no room for them the arena stays as it is.  When the previous
 // direct call ran on another stream, `s` first waits for that call's work, so calls on different
 // streams never share the scratch in time.
 int arena_reserve(dc_ctx *ctx, size_t bytes, hipStream_t s);

@@ -535,7 +535,7 @@ static int dev_grow(Scheduler *S, size_t need, bool exact) {
     }
     const size_t want = exact ? need : std::min(std::max(need, S->dev_seg), room);
     void *p = nullptr;
-    const int rc = dev_alloc_raw(ctx, &p, want);
+    const int rc = dev_alloc(ctx, &p, want);
     if (rc != DC_OK) return rc;
     S->dpool.add(static_cast<char *>(p), want);
     return DC_OK;
@@ -774,7 +774,7 @@ static int init_slot(Scheduler *S, BatchSlot &sl) {
     DC_HIP(hipStreamCreateWithFlags(&sl.stream, hipStreamNonBlocking));
     DC_HIP(hipEventCreateWithFlags(&sl.ev, hipEventDisableTiming));
     void *p = nullptr;
-    const int rc = dev_alloc_raw(S->ctx, &p, sizeof(BatchDesc));
+    const int rc = dev_alloc(S->ctx, &p, sizeof(BatchDesc));
     if (rc != DC_OK) return rc;
     sl.d_desc = static_cast<BatchDesc *>(p);
     DC_HIP(hipHostMalloc(reinterpret_cast<void **>(&sl.h_desc), sizeof(BatchDesc), 0));

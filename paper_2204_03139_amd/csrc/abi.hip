@@ -1,5 +1,6 @@
 // C ABI entry points of libdiffcloud: argument validation, scratch management under the HBM
 // budget, and the launch sequence of each call.  Every kernel runs on the caller's stream.
+#include <algorithm>
 #include <cstdio>
 #include <cstring>
 #include <new>
@@ -66,13 +67,24 @@ void dev_free(dc_ctx *ctx, void *p, size_t bytes) {
     budget_give(ctx, bytes);
 }
 
-int arena_reserve(dc_ctx *ctx, size_t bytes, hipStream_t s) {
+static size_t arena_size(size_t bytes) {
+    return (bytes + (size_t(1) << 20) - 1) & ~((size_t(1) << 20) - 1);
+}
+
+int arena_reserve(dc_ctx *ctx, size_t bytes, size_t plain, hipStream_t s) {
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &st) != hipSuccess) (void)hipGetLastError();
+    if (st != hipStreamCaptureStatusNone) ctx->arena_captured = true;
     if (ctx->arena_used && s != ctx->arena_stream)
         DC_HIP(hipStreamWaitEvent(s, ctx->arena_ev, 0));
     Arena &a = ctx->arena;
     a.reset();
-    if (bytes <= a.cap) return DC_OK;
-    const size_t want = (bytes + (size_t(1) << 20) - 1) & ~((size_t(1) << 20) - 1);
+    plain = std::max(ctx->arena_plain, std::min(plain, bytes));
+    if (bytes <= a.cap) {
+        ctx->arena_plain = plain;
+        return DC_OK;
+    }
+    const size_t want = arena_size(bytes);
     // A size that cannot be had leaves the buffer as it is: a call that then makes do with less scratch
     // finds it there, and neither waits nor allocates on each call.
     {
@@ -104,7 +116,22 @@ int arena_reserve(dc_ctx *ctx, size_t bytes, hipStream_t s) {
     if (rc != DC_OK) return rc;
     a.base = static_cast<char *>(p);
     a.cap = want;
+    ctx->arena_plain = plain;
     return DC_OK;
+}
+
+bool arena_trim(dc_ctx *ctx) {
+    Arena &a = ctx->arena;
+    const size_t keep = arena_size(ctx->arena_plain);
+    if (a.cap <= keep || ctx->arena_captured || hipDeviceSynchronize() != hipSuccess) return false;
+    dev_free(ctx, a.base, a.cap);
+    a = Arena();
+    void *p = nullptr;
+    if (keep && dev_alloc(ctx, &p, keep) == DC_OK) {
+        a.base = static_cast<char *>(p);
+        a.cap = keep;
+    }
+    return true;
 }
 
 ArenaUse::~ArenaUse() {
@@ -502,7 +529,10 @@ int dc_chamfer_fwd(dc_ctx *ctx, const float *a, const float *b, int T, int Na, i
     std::lock_guard<std::mutex> g(ctx->mu);
     Search search = plan_search(T, Na, Nb, precision, idx_b != nullptr, true);
     size_t need = search_scratch_bytes(search, T, Na, Nb);
-    rc = arena_reserve(ctx, need, static_cast<hipStream_t>(stream));
+    // (without the ordered clouds, a call keeps room for its precision's own search)
+    const size_t plain = search_scratch_bytes(
+        precision == DC_PREC_BF16_REFINE ? Search::screen : Search::exact, T, Na, Nb);
+    rc = arena_reserve(ctx, need, plain, static_cast<hipStream_t>(stream));
     if ((rc == DC_ERR_BUDGET || rc == DC_ERR_NOMEM) && search == Search::ordered) {
         // the other searches may need less than the ordered clouds
         search = plan_search(T, Na, Nb, precision, idx_b != nullptr, false);

@@ -63,6 +63,8 @@ struct dc_ctx {
     std::mutex budget_mu;         // guards budget accounting
     size_t held = 0;              // bytes of device memory held against the budget
     dc::Arena arena;              // scratch of direct calls
+    size_t arena_plain = 0;       // the most that calls asked for which could not do with less
+    bool arena_captured = false;  // a call was captured: a graph may hold the arena's address
     hipEvent_t arena_ev = nullptr;        // recorded after each direct call's work on its stream
     hipStream_t arena_stream = nullptr;   // the stream of the last direct call
     bool arena_used = false;
@@ -97,10 +99,16 @@ bool forced_alloc_failure(dc_ctx *ctx);
 int dev_alloc(dc_ctx *ctx, void **p, size_t bytes);
 void dev_free(dc_ctx *ctx, void *p, size_t bytes);
 // Make sure the direct-call arena holds at least `bytes` and reset its offset; where the budget or the
-// device has no room for them the arena stays as it is.  When the previous
+// device has no room for them the arena stays as it is.  `plain`: what the call can do with.  When the previous
 // direct call ran on another stream, `s` first waits for that call's work, so calls on different
 // streams never share the scratch in time.
-int arena_reserve(dc_ctx *ctx, size_t bytes, hipStream_t s);
+int arena_reserve(dc_ctx *ctx, size_t bytes, size_t plain, hipStream_t s);
+inline int arena_reserve(dc_ctx *ctx, size_t bytes, hipStream_t s) {
+    return arena_reserve(ctx, bytes, bytes, s);
+}
+// Give back what the arena holds beyond the calls' plain needs, for the serving loop where the budget has
+// no other room (ctx->mu held).  Whether there was anything.
+bool arena_trim(dc_ctx *ctx);
 // mark the end of a direct call's use of the arena (records the arena event on `s`)
 struct ArenaUse {
     dc_ctx *ctx;

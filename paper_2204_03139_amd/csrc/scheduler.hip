@@ -563,7 +563,7 @@ static int admit(Scheduler *S, Req *r) {
             // for one that holds this request exactly
             dev_release_all(S);
             rc = dev_grow(S, n, true);
-            if (rc == DC_ERR_BUDGET && r->search == Search::ordered) {
+            if ((rc == DC_ERR_BUDGET || rc == DC_ERR_NOMEM) && r->search == Search::ordered) {
                 // beside the direct calls' scratch the budget may still hold the request without
                 // its ordered clouds (the inputs and outputs keep their places in the region)
                 r->search = request_search(r->T, r->Na, r->Nb, r->precision, r->reduction, false);
@@ -571,6 +571,11 @@ static int admit(Scheduler *S, Req *r) {
                                     r->want_grad);
                 n = r->map.total;
                 rc = dev_grow(S, n, true);
+            }
+            if (rc == DC_ERR_BUDGET) {
+                // the direct calls may hold room for ordered clouds that they can do without
+                std::lock_guard<std::mutex> g(S->ctx->mu);
+                if (arena_trim(S->ctx)) rc = dev_grow(S, n, true);
             }
             if (rc != DC_OK) return rc;
         }
@@ -877,7 +882,8 @@ int sched_submit(dc_ctx *ctx, const dc_request *q, dc_result *out, uint64_t *tic
     Scheduler *S = nullptr;
     {
         std::lock_guard<std::mutex> g(ctx->mu);  // creation of the loop is serialised with direct calls
-        const int rc = ensure_scheduler(ctx);
+        int rc = ensure_scheduler(ctx);
+        if (rc == DC_ERR_BUDGET && arena_trim(ctx)) rc = ensure_scheduler(ctx);
         if (rc) return rc;
         S = ctx->sched;
     }

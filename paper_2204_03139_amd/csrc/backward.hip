@@ -1,7 +1,7 @@
 // Backward passes: the Chamfer gradient through the saved neighbours (Sec. III-A, Eq. 1/2) and
 // the sampling gradient through Eq. 4 (Sec. III-B).  Both are gathers over segments of equal keys
 // (listed in LDS, or for very many items built by a stable sort), each put into increasing index
-// order first and summed in an order fixed by that, in double (each output rounded
+// order first and summed in an order fixed by that and by the sizes, in double (each output rounded
 // once to float), so every result is bitwise reproducible, independent of scheduling, and within a
 // few units of 2^-24 of the sum of its terms' magnitudes however long a segment is.
 #include <algorithm>
@@ -335,7 +335,7 @@ __device__ __forceinline__ void grouped_sums(const int32_t *__restrict__ keys, i
             }
             ke = lo;
         }
-        // a key with more items than fit: by all threads, each its every 1,024th item
+        // a key with more items than fit: by all threads, each its every TH-th item
         const bool giant = ke == kb;
         if (giant) ke = kb + 1;
         const int total = s.start[ke] - base;
@@ -666,14 +666,21 @@ void launch_chamfer_bwd(const double *grad_loss, const float *a, const float *b,
         gp.side[1] = {b, beta != 0.0 ? idx_b : nullptr, grad_b, Nb, pb.keys, pb.team, 0};
         gp.cself[0] = 2.0 * alpha;
         gp.cself[1] = 2.0 * beta;
-        gp.first = group_a ? 0 : 1;
         gp.pad = 0;
-        // one launch for both sides; a small workgroup's range also fits a large one
-        const int threads = std::max(group_a ? pa.threads : 0, group_b ? pb.threads : 0);
-        dispatch_group(KT_GROUP_CHAMFER, k_group_chamfer<GP_SMALL>, k_group_chamfer<GP_LARGE>, threads,
-                       dim3(std::max(group_a ? pa.ranges : 0, group_b ? pb.ranges : 0), T,
-                            group_a && group_b ? 2 : 1),
-                       gp, s);
+        auto launch = [&](int first, int sides, int threads, int ranges) {
+            gp.first = first;
+            dispatch_group(KT_GROUP_CHAMFER, k_group_chamfer<GP_SMALL>, k_group_chamfer<GP_LARGE>,
+                           threads, dim3(ranges, T, sides), gp, s);
+        };
+        // One launch for both sides where they take workgroups of one size.  The size decides how a key of
+        // many items is summed, so a side keeps its own: its sums don't depend on whether the other side's
+        // are wanted.
+        if (group_a && group_b && pa.threads == pb.threads) {
+            launch(0, 2, pa.threads, std::max(pa.ranges, pb.ranges));
+        } else {
+            if (group_a) launch(0, 1, pa.threads, pa.ranges);
+            if (group_b) launch(1, 1, pb.threads, pb.ranges);
+        }
     }
     ChamferBwdParams cp;
     cp.grad_loss = grad_loss;

@@ -214,6 +214,7 @@ constexpr int GP_SMALL = 512, GP_LARGE = 1024;
 constexpr int GP_WIDE = 49152;
 constexpr int GP_IBITS = 17;      // bits of an item in a listed word, below its key
 constexpr int GP_MAX = 1 << GP_IBITS;
+constexpr float GP_HEAVY = 12.f;
 
 // items listed at once, and most keys, of a workgroup of TH threads
 template <int TH>
@@ -232,8 +233,17 @@ struct GroupLds {
         float row[3][gp_cap<TH>()];  // in their place, what the items stand for
     };
     int wsum[TH / 64];
+    int heavy;  // the first heavy key of a round; before the rounds: whether there is one
     double part[TH / 64][9];
 };
+
+// Whether a key of `len` of n items is heavy: summed by the whole workgroup, where the comparisons of its items
+// with each other, len^2 over all threads, would take longer than two more passes over the n keys.  More items
+// than a list holds always are.
+__device__ __forceinline__ bool heavy_key(int len, int n) {
+    return (float)len * (float)len > GP_HEAVY * (float)n;
+}
+static_assert((float)gp_cap<GP_SMALL>() * gp_cap<GP_SMALL>() > GP_HEAVY * GP_MAX, "a list holds a light key");
 
 // a sum of M components by the G lanes of a key's team (in every lane), in a fixed order
 template <int M>
@@ -275,52 +285,21 @@ struct Row3 {
 
 // For every key in [k0, k0 + nk): `own(key)` reads what the key itself needs, `each(own, item, on, sum)`
 // adds what `fetch(item)` gives to its sum (nothing unless `on`), `put(key, own, sum)` takes the total; at
-// least G lanes share a key.  A round lists as many keys as fit CAP items; a key with more is summed by the whole
-// workgroup, straight from the keys, each thread its every TH-th item.  Rows of three floats (STAGE) are
+// least G lanes share a key.  A round lists as many keys as fit CAP items.  Rows of three floats (STAGE) are
 // fetched into LDS before the sums, by all lanes and four at a time: fetched by the lanes of a key, most
 // of a wave's lanes wait for its longest key, and two keys in hand to fill the waits spilled registers
 // (Chamfer backward of 100 x 65,536 points 256 -> 191 us, of 40 x 8,192 18.2 -> 12.7 us).
-template <int TH, int M, bool STAGE, class Own, class Fetch, class Each, class Put>
-__device__ __forceinline__ void grouped_sums(const int32_t *__restrict__ keys, int n, int k0, int nk,
-                                             int G, GroupLds<TH> &s, const Own &own, const Fetch &fetch,
-                                             const Each &each, const Put &put) {
+//
+// A heavy key has a round and the whole workgroup for itself: its items listed thread by thread, or, where
+// they are more than fit, straight from the keys, each thread its every TH-th item.  20 of 19,602 faces with
+// all of a frame's 65,536 points take 350 us, ranked like the others 4,460 us.  Rounds for ranges without
+// one (HEAVY false) are compiled by themselves: in common code the other branch's registers spilled.
+template <int TH, int M, bool STAGE, bool HEAVY, class Own, class Fetch, class Each, class Put>
+__device__ __forceinline__ void sum_rounds(const int32_t *__restrict__ keys, int n, int k0, int nk, int G,
+                                           GroupLds<TH> &s, const Own &own, const Fetch &fetch,
+                                           const Each &each, const Put &put) {
     constexpr int CAP = gp_cap<TH>(), WAVES = TH / 64;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    for (int k = tid; k < nk; k += TH) s.cursor[k] = 0;
-    __syncthreads();
-    each_key<TH>(keys, n, [&](int i, int key) {
-        const int k = key - k0;
-        if ((unsigned)k < (unsigned)nk) atomicAdd(&s.cursor[k], 1);
-    });
-    __syncthreads();
-    {  // counts to starts
-        constexpr int PER = CAP / TH;
-        int c[PER], sum = 0;
-#pragma unroll
-        for (int u = 0; u < PER; ++u) {
-            const int k = tid * PER + u;
-            c[u] = k < nk ? s.cursor[k] : 0;
-            sum += c[u];
-        }
-        int incl = sum;
-#pragma unroll
-        for (int off = 1; off < 64; off <<= 1) {
-            const int o = __shfl_up(incl, off, 64);
-            if (lane >= off) incl += o;
-        }
-        if (lane == 63) s.wsum[wave] = incl;
-        __syncthreads();
-        int at = incl - sum;
-        for (int w = 0; w < wave; ++w) at += s.wsum[w];
-#pragma unroll
-        for (int u = 0; u < PER; ++u) {
-            const int k = tid * PER + u;
-            if (k <= nk) s.start[k] = at;
-            at += c[u];
-        }
-        if (tid == TH - 1 && nk == CAP) s.start[nk] = at;
-        __syncthreads();
-    }
     for (int kb = 0; kb < nk;) {
         const int base = s.start[kb];
         int ke = nk;  // the keys of the round: the last one whose items still fit
@@ -335,11 +314,37 @@ __device__ __forceinline__ void grouped_sums(const int32_t *__restrict__ keys, i
             }
             ke = lo;
         }
-        // a key with more items than fit: by all threads, each its every TH-th item
-        const bool giant = ke == kb;
-        if (giant) ke = kb + 1;
+        bool heavy = false;
+        if (HEAVY) {  // the round ends before a heavy key, or is one
+            __syncthreads();
+            if (tid == 0) s.heavy = nk;
+            __syncthreads();
+            for (int k = kb + tid; k < max(ke, kb + 1); k += TH)
+                if (heavy_key(s.start[k + 1] - s.start[k], n)) atomicMin(&s.heavy, k);
+            __syncthreads();
+            heavy = s.heavy == kb;
+            ke = heavy ? kb + 1 : min(ke, s.heavy);
+        }
         const int total = s.start[ke] - base;
-        if (total > 0 && !giant) {
+        const bool over = HEAVY && total > CAP, listed = total > 0 && !over;
+        if (listed && heavy) {
+            int mine = 0;
+            each_key<TH>(keys, n, [&](int, int key) { mine += key == k0 + kb ? 1 : 0; });
+            int at = mine;
+#pragma unroll
+            for (int off = 1; off < 64; off <<= 1) {
+                const int o = __shfl_up(at, off, 64);
+                if (lane >= off) at += o;
+            }
+            if (lane == 63) s.wsum[wave] = at;
+            __syncthreads();
+            at -= mine;
+            for (int w = 0; w < wave; ++w) at += s.wsum[w];
+            each_key<TH>(keys, n, [&](int i, int key) {
+                if (key == k0 + kb) s.item[at++] = i;
+            });
+            __syncthreads();
+        } else if (listed) {
             for (int k = kb + tid; k < ke; k += TH) s.cursor[k] = s.start[k] - base;
             __syncthreads();
             each_key<TH>(keys, n, [&](int i, int key) {
@@ -360,7 +365,7 @@ __device__ __forceinline__ void grouped_sums(const int32_t *__restrict__ keys, i
             __syncthreads();
         }
         if constexpr (STAGE) {
-            if (total > 0 && !giant) {
+            if (listed) {
                 constexpr int PER = CAP / TH;
                 decltype(fetch(0)) f[PER];
 #pragma unroll
@@ -374,7 +379,7 @@ __device__ __forceinline__ void grouped_sums(const int32_t *__restrict__ keys, i
                 __syncthreads();
             }
         }
-        if (giant) {
+        if (over) {
             const auto whole = own(k0 + kb);
             double v[M];
 #pragma unroll
@@ -388,16 +393,17 @@ __device__ __forceinline__ void grouped_sums(const int32_t *__restrict__ keys, i
             __syncthreads();
         }
         // Lanes per key: G, and more where the round's keys have far more items than the average key that G
-        // is for (a few neighbouring keys then hold most items, and most lanes would have none: 20 of
-        // 19,602 faces with all of 65,536 points 6,500 us with four lanes a face).
+        // is for (a few neighbouring keys then hold most items, and most lanes would have none: points of 50
+        // of 4,802 faces, 8,192 of them, 102 us with four lanes a face, 47 with more).
         int team = G;
         while (team < 64 && total > 8 * team * (ke - kb) && 2 * team * (ke - kb) <= TH) team *= 2;
+        if (heavy) team = TH;
         const int per = TH / team, l = tid & (team - 1);
 #pragma unroll 1
-        for (int k = giant ? kb + tid : kb + tid / team; k < ke; k += per) {
+        for (int k = kb + tid / team; k < ke; k += per) {
             double v[M];
             const auto mine = own(k0 + k);
-            const int hi = giant ? 0 : s.start[k + 1] - base;
+            const int hi = over ? 0 : s.start[k + 1] - base;
 #pragma unroll
             for (int m = 0; m < M; ++m) v[m] = 0.0;
 #pragma unroll 1
@@ -410,18 +416,72 @@ __device__ __forceinline__ void grouped_sums(const int32_t *__restrict__ keys, i
                     f = fetch(s.item[e]);
                 each(mine, f, true, v);
             }
-            if (!giant)
-                team_sum(v, team);
-            else  // by lane 0 alone, from the waves' sums
+            team_sum(v, min(team, 64));
+            if (heavy) {  // one key, so all threads are here
+                if (!over && lane == 0)
+#pragma unroll
+                    for (int m = 0; m < M; ++m) s.part[wave][m] = v[m];
+                __syncthreads();
 #pragma unroll 1
-                for (int w = 0; w < WAVES; ++w)
+                for (int w = over ? 0 : 1; w < WAVES; ++w)
 #pragma unroll
                     for (int m = 0; m < M; ++m) v[m] += s.part[w][m];
+            }
             if (l == 0) put(k0 + k, mine, v);
         }
         __syncthreads();  // the next round lists anew
         kb = ke;
     }
+}
+
+template <int TH, int M, bool STAGE, class Own, class Fetch, class Each, class Put>
+__device__ __forceinline__ void grouped_sums(const int32_t *__restrict__ keys, int n, int k0, int nk,
+                                             int G, GroupLds<TH> &s, const Own &own, const Fetch &fetch,
+                                             const Each &each, const Put &put) {
+    constexpr int CAP = gp_cap<TH>();
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    for (int k = tid; k < nk; k += TH) s.cursor[k] = 0;
+    if (tid == 0) s.heavy = 0;
+    __syncthreads();
+    each_key<TH>(keys, n, [&](int i, int key) {
+        const int k = key - k0;
+        if ((unsigned)k < (unsigned)nk) atomicAdd(&s.cursor[k], 1);
+    });
+    __syncthreads();
+    {  // counts to starts
+        constexpr int PER = CAP / TH;
+        int c[PER], sum = 0, most = 0;
+#pragma unroll
+        for (int u = 0; u < PER; ++u) {
+            const int k = tid * PER + u;
+            c[u] = k < nk ? s.cursor[k] : 0;
+            sum += c[u];
+            most = max(most, c[u]);
+        }
+        if (heavy_key(most, n)) s.heavy = 1;
+        int incl = sum;
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            const int o = __shfl_up(incl, off, 64);
+            if (lane >= off) incl += o;
+        }
+        if (lane == 63) s.wsum[wave] = incl;
+        __syncthreads();
+        int at = incl - sum;
+        for (int w = 0; w < wave; ++w) at += s.wsum[w];
+#pragma unroll
+        for (int u = 0; u < PER; ++u) {
+            const int k = tid * PER + u;
+            if (k <= nk) s.start[k] = at;
+            at += c[u];
+        }
+        if (tid == TH - 1 && nk == CAP) s.start[nk] = at;
+        __syncthreads();
+    }
+    if (s.heavy)
+        sum_rounds<TH, M, STAGE, true>(keys, n, k0, nk, G, s, own, fetch, each, put);
+    else
+        sum_rounds<TH, M, STAGE, false>(keys, n, k0, nk, G, s, own, fetch, each, put);
 }
 
 // keys per workgroup, workgroups, and lanes per key for `n` items of `K` keys, `sets` times over

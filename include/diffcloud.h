@@ -236,10 +236,13 @@ int dc_rigid_pose_bwd(dc_ctx *ctx, const double *q, const float *p0, const int32
 
 /* Counters of the DC_PREC_BF16_REFINE searches since the context was created (read after dc_sync):
  *   queries    nearest-neighbour queries answered by the ordered or the screened search
- *   candidates candidate groups re-evaluated exactly (ordered: one per query, the 16 points around
- *              its minimum)
- *   fallbacks  queries searched a second time: whose certificate failed (screen), or whose minimum
- *              was met more than once (ordered) */
+ *   candidates candidate groups re-evaluated exactly (ordered: groups of 16 points that may hold a
+ *              query's minimum)
+ *   fallbacks  queries searched a second time: whose certificate failed (screen), whose minimum
+ *              more groups may hold than are remembered, or whose wave was swept for others of its
+ *              queries (ordered); where few query waves are shared by many waves, those whose minimum
+ *              was met more than once.  Candidates and fallbacks of ordered clouds vary a little from
+ *              run to run: the order of points within a cell does (the results don't).  */
 typedef struct dc_stats {
     uint64_t queries;
     uint64_t candidates;

@@ -865,11 +865,19 @@ constexpr float NEAR_SAFE = 1e30f;  // |q'|^2 and v up to which nothing overflow
 // points 264 and 302 us (ordering included, both directions).
 constexpr int NEAR_FEW = 3;
 
-// The end of a search: the queries without a finite distance, the results and the counters.
+// Adds n to a counter: 0 queries, 1 sub-tiles read again, 2 queries searched again.
+__device__ __forceinline__ void near_count(const NearParams &pr, int lane, int which, unsigned long long n) {
+    if (pr.stats && lane == 0 && n)
+        atomicAdd(pr.stats + (size_t)((blockIdx.x + gridDim.x * blockIdx.y) % STATS_SLOTS) * STATS_SLOT_WORDS +
+                      which,
+                  n);
+}
+
+// The end of a search: the queries without a finite distance, and the results.  The first wave counts the
+// call's queries, and one sub-tile read again for each.
 __device__ __forceinline__ void near_finish(const NearParams &pr, const Blk &blk, const NearCloud &qc,
                                             const NearCloud &pc, int lane, bool writes, bool first,
-                                            const nfloat4 &q, float best, int found, bool finite,
-                                            unsigned ties) {
+                                            const nfloat4 &q, float best, int found, bool finite) {
     const int t = blk.y, qi = __float_as_int(q.w);
     const float inf = __builtin_inff();
     // no finite distance: the first of the first 64 targets at an infinite distance, or target 0
@@ -896,16 +904,11 @@ __device__ __forceinline__ void near_finish(const NearParams &pr, const Blk &blk
         qc.idx[o] = found;
         qc.dist[o] = best;
     }
-    if (pr.stats && lane == 0) {
-        unsigned long long *slot =
-            pr.stats + (size_t)((blockIdx.x + gridDim.x * blockIdx.y) % STATS_SLOTS) * STATS_SLOT_WORDS;
-        if (first) {  // the call's queries, one sub-tile read again each
-            const unsigned long long all =
-                (unsigned long long)blk.gy * (pr.c[0].n + (pr.both ? pr.c[1].n : 0));
-            atomicAdd(&slot[0], all);
-            atomicAdd(&slot[1], all);
-        }
-        if (ties) atomicAdd(&slot[2], (unsigned long long)ties);
+    if (first) {
+        const unsigned long long all =
+            (unsigned long long)blk.gy * (pr.c[0].n + (pr.both ? pr.c[1].n : 0));
+        near_count(pr, lane, 0, all);
+        near_count(pr, lane, 1, all);
     }
 }
 
@@ -1092,7 +1095,6 @@ __device__ __forceinline__ void near_shared_body(const NearParams &pr, const Blk
     }
     // a minimum met in more than one sub-tile: every point at exactly that distance
     unsigned long long again = __ballot(finite && tie);
-    unsigned ties = (unsigned)__popcll(again);
     const bool same = one_point(Q);  // as in near_body
     if (same) again &= ~again + 1;
     while (again) {
@@ -1133,12 +1135,16 @@ __device__ __forceinline__ void near_shared_body(const NearParams &pr, const Blk
     if (finite && (atomicMin(&sidx[group][lane], found) != 0x7fffffff || tie))
         stie[group][lane] = 1;
     __syncthreads();
-    ties = r == 0 ? (unsigned)__popcll(__ballot(stie[group][lane])) : 0u;
+    if (r == 0) {  // queries whose minimum was met more than once
+        const int ties = __popcll(__ballot(stie[group][lane]));
+        near_count(pr, lane, 1, ties);
+        near_count(pr, lane, 2, ties);
+    }
     found = sidx[group][lane];
     best = bound;
     finite = live && bound < inf;
     near_finish(pr, blk, qc, pc, lane, r == 0, blk.x == 0 && t == 0 && wave == 0, q, best, found,
-                finite, ties);
+                finite);
 }
 
 // The search of waves that have their queries to themselves, blocks screened on the matrix cores.
@@ -1228,9 +1234,7 @@ __device__ __forceinline__ void near_body(const NearParams &pr, const Blk &blk) 
     // The canonical distances, and the smallest original index at the smallest.
     float best = inf;
     int found = 0x7fffffff;
-    bool tie = false;
     auto meet = [&](float e, int i) {
-        tie = e < best ? false : (tie || (e == best && i != found));
         found = e < best ? i : (e == best ? min(found, i) : found);
         best = fminf(best, e);
     };
@@ -1348,11 +1352,15 @@ __device__ __forceinline__ void near_body(const NearParams &pr, const Blk &blk) 
             }
             // the sub-tiles that may hold the smallest distance
             const bool known = live && __uint_as_float(m1) < NEAR_SAFE;
+            bool two = false;
             if (known) {
                 refine(at1);
-                if (__uint_as_float(m2) <= limit(best)) refine(at2);
+                two = __uint_as_float(m2) <= limit(best);
+                if (two) refine(at2);
             }
+            near_count(pr, lane, 1, __popcll(__ballot(two)));
             again = __ballot(live && (!known || __uint_as_float(m3) <= limit(best)));
+            near_count(pr, lane, 2, __popcll(again));
             if (same) again &= ~again + 1;
         }
         // More sub-tiles than that for some queries, or values that may have overflowed: every point
@@ -1373,6 +1381,7 @@ __device__ __forceinline__ void near_body(const NearParams &pr, const Blk &blk) 
             // of the last tested super-block hardly a block was ruled out by the queries' own distances:
             // then three of four super-blocks go untested (a quarter of the sweep's time)
             bool all = false;
+            near_count(pr, lane, 2, __popcll(__ballot(live) & ~again));  // the others of the wave
             for (int c = 0; c < chunks; ++c) {
                 const int g = c * 64 + lane;
                 float far = wave_max(live ? best : -1.f);
@@ -1476,19 +1485,16 @@ __device__ __forceinline__ void near_body(const NearParams &pr, const Blk &blk) 
                 bl = wave_min(low);
             }
         }
-        const unsigned long long hits = __ballot(low == bl && mine != 0x7fffffff);
         if (low != bl) mine = 0x7fffffff;
 #pragma unroll
         for (int off = 32; off > 0; off >>= 1) mine = min(mine, __shfl_xor(mine, off, 64));
         if (lane == l || (same && live)) {
-            tie = __popcll(hits) > 1;
             found = mine;
             best = bl;
         }
     }
     const bool finite = live && best < inf;
-    near_finish(pr, blk, qc, pc, lane, true, blk.x == 0 && t == 0, q, best, found, finite,
-                (unsigned)__popcll(__ballot(finite && tie)));
+    near_finish(pr, blk, qc, pc, lane, true, blk.x == 0 && t == 0, q, best, found, finite);
 }
 
 // For few frames, the grid with each XCD given a contiguous eighth of each side's workgroups: one side may

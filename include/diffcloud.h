@@ -336,6 +336,15 @@ int dc_memory_held(dc_ctx *ctx, size_t *held, size_t *budget);
  * request then fails alone). */
 int dc_debug_fail_allocs(dc_ctx *ctx, int n);
 
+/* Test hook: the nearest-neighbour search of the context's calls and of requests submitted from now
+ * on.  All give the same results; the library otherwise takes the fastest (DC_DEBUG_PLANNED).
+ * Errors: DC_ERR_INVALID. */
+#define DC_DEBUG_PLANNED 0
+#define DC_DEBUG_ORDERED 1 /* over spatially ordered clouds */
+#define DC_DEBUG_SCREEN 2  /* bf16 matrix-core screen and exact re-evaluation */
+#define DC_DEBUG_EXACT 3   /* every pair in single precision */
+int dc_debug_search(dc_ctx *ctx, int search);
+
 /* Library version as major*10000 + minor*100 + patch. */
 int dc_version(void);
 

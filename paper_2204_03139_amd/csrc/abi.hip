@@ -210,7 +210,12 @@ size_t search_scratch_bytes(Search search, int T, int Na, int Nb) {
 // frames of many rows against a handful of targets (one frame of 32,768 x 64: 103 us against 145 us
 // for the exact search and 129 us for the ordered one; 32 frames: 317 against 106 us), and where
 // the exact search would need more scratch.
-Search plan_search(int T, int Na, int Nb, int precision, bool two, bool ordering) {
+Search plan_search(const dc_ctx *ctx, int T, int Na, int Nb, int precision, bool two, bool ordering) {
+    switch (ctx ? ctx->debug_search : 0) {
+        case DC_DEBUG_ORDERED: return Search::ordered;
+        case DC_DEBUG_SCREEN: return Search::screen;
+        case DC_DEBUG_EXACT: return Search::exact;
+    }
     if (ordering && ordered_pays(T, Na, Nb, two)) return Search::ordered;
     if (precision == DC_PREC_BF16_REFINE &&
         ((Na >= 8192 && (long)T * Na <= 65536) ||
@@ -415,6 +420,13 @@ int dc_debug_fail_allocs(dc_ctx *ctx, int n) {
     return DC_OK;
 }
 
+int dc_debug_search(dc_ctx *ctx, int search) {
+    if (!ctx || search < DC_DEBUG_PLANNED || search > DC_DEBUG_EXACT) return DC_ERR_INVALID;
+    std::lock_guard<std::mutex> g(ctx->mu);
+    ctx->debug_search = search;
+    return DC_OK;
+}
+
 static int sample_surface_impl(dc_ctx *ctx, const float *verts, const int32_t *faces, int T,
                                int V, int F, int N, uint64_t seed, const uint32_t *uniforms,
                                const uint8_t *mask, int mask_per_frame, float *points,
@@ -527,7 +539,7 @@ int dc_chamfer_fwd(dc_ctx *ctx, const float *a, const float *b, int T, int Na, i
     if (rc) return rc;
     DC_HIP(hipSetDevice(ctx->device));
     std::lock_guard<std::mutex> g(ctx->mu);
-    Search search = plan_search(T, Na, Nb, precision, idx_b != nullptr, true);
+    Search search = plan_search(ctx, T, Na, Nb, precision, idx_b != nullptr, true);
     size_t need = search_scratch_bytes(search, T, Na, Nb);
     // (without the ordered clouds, a call keeps room for its precision's own search)
     const size_t plain = search_scratch_bytes(
@@ -535,7 +547,7 @@ int dc_chamfer_fwd(dc_ctx *ctx, const float *a, const float *b, int T, int Na, i
     rc = arena_reserve(ctx, need, plain, static_cast<hipStream_t>(stream));
     if ((rc == DC_ERR_BUDGET || rc == DC_ERR_NOMEM) && search == Search::ordered) {
         // the other searches may need less than the ordered clouds
-        search = plan_search(T, Na, Nb, precision, idx_b != nullptr, false);
+        search = plan_search(ctx, T, Na, Nb, precision, idx_b != nullptr, false);
         need = search_scratch_bytes(search, T, Na, Nb);
         clear_error();
         rc = arena_reserve(ctx, need, static_cast<hipStream_t>(stream));

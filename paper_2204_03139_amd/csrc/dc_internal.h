@@ -72,6 +72,7 @@ struct dc_ctx {
     unsigned long long *d_stats = nullptr;  // screen counters: [STATS_SLOTS][STATS_SLOT_WORDS]
     dc::Scheduler *sched = nullptr;
     int fail_next_alloc = 0;      // test hook: make the next N allocations fail
+    int debug_search = 0;         // test hook: the search of every Chamfer call (0: as planned)
     bool prof = false;            // record events around profiled launches
     std::mutex prof_mu;
     std::vector<dc::ProfRecord> prof_pending;
@@ -215,7 +216,7 @@ int enqueue_sample(dc_ctx *prof, const float *verts, const int32_t *faces, int T
 // directions are wanted; `ordering`: whether the search over ordered clouds may be chosen (its
 // scratch can be larger than the exact search's).
 enum class Search { ordered, screen, exact };
-Search plan_search(int T, int Na, int Nb, int precision, bool two, bool ordering);
+Search plan_search(const dc_ctx *ctx, int T, int Na, int Nb, int precision, bool two, bool ordering);
 size_t search_scratch_bytes(Search search, int T, int Na, int Nb);
 int enqueue_chamfer_fwd(dc_ctx *prof, const float *a, const float *b, int T, int Na, int Nb,
                         Search search, bool count,

@@ -225,8 +225,9 @@ struct RegionMap {
 
 // the search of a request; `ordering` false: without the scratch of ordered clouds, for a budget
 // that holds the request no other way
-Search request_search(int T, int Na, int Nb, int precision, int reduction, bool ordering) {
-    return plan_search(T, Na, Nb, precision, reduction != DC_RED_SIM2REAL_SUM, ordering);
+Search request_search(const dc_ctx *ctx, int T, int Na, int Nb, int precision, int reduction,
+                      bool ordering) {
+    return plan_search(ctx, T, Na, Nb, precision, reduction != DC_RED_SIM2REAL_SUM, ordering);
 }
 
 // A request keeps room for any of its precision's searches beside the one it will run, so what
@@ -490,7 +491,7 @@ struct Scheduler {
 size_t request_bytes(int T, int V, int F, int Na, int Nb, int precision, int reduction,
                      bool want_grad) {
     return region_map(T, V, F, Na, Nb, precision,
-                      request_search(T, Na, Nb, precision, reduction, true), want_grad)
+                      request_search(nullptr, T, Na, Nb, precision, reduction, true), want_grad)
         .total;
 }
 
@@ -566,7 +567,8 @@ static int admit(Scheduler *S, Req *r) {
             if ((rc == DC_ERR_BUDGET || rc == DC_ERR_NOMEM) && r->search == Search::ordered) {
                 // beside the direct calls' scratch the budget may still hold the request without
                 // its ordered clouds (the inputs and outputs keep their places in the region)
-                r->search = request_search(r->T, r->Na, r->Nb, r->precision, r->reduction, false);
+                r->search = request_search(S->ctx, r->T, r->Na, r->Nb, r->precision, r->reduction,
+                                           false);
                 r->map = region_map(r->T, r->V, r->F, r->Na, r->Nb, r->precision, r->search,
                                     r->want_grad);
                 n = r->map.total;
@@ -870,7 +872,8 @@ int sched_submit(dc_ctx *ctx, const dc_request *q, dc_result *out, uint64_t *tic
     RegionMap map;
     Search search;
     for (int ordering = 1; ordering >= 0; --ordering) {
-        search = request_search(q->T, q->n_sim, q->n_obs, q->precision, q->reduction, ordering != 0);
+        search = request_search(ctx, q->T, q->n_sim, q->n_obs, q->precision, q->reduction,
+                                ordering != 0);
         map = region_map(q->T, q->V, q->F, q->n_sim, q->n_obs, q->precision, search, want_grad);
         if (map.total + serving_fixed_bytes() + CTX_WORDS_BYTES <= ctx->budget) break;
     }

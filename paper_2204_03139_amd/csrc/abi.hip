@@ -206,20 +206,22 @@ size_t search_scratch_bytes(Search search, int T, int Na, int Nb) {
 }
 
 // The search over ordered clouds wherever it is the faster one (ordered_pays), in either precision.
-// Of the other calls, the bf16 ones keep the screen where it is still the faster: one to a few
-// frames of many rows against a handful of targets (one frame of 32,768 x 64: 103 us against 145 us
-// for the exact search and 129 us for the ordered one; 32 frames: 317 against 106 us), and where
-// the exact search would need more scratch.
+// The bf16 calls keep the screen where it is still the faster: both directions of one to four frames of
+// rows by the ten thousand against 32 to 128 targets (one frame of 65,536 x 64: 116 us against 153 for
+// every pair and 194 for the ordered search; of 32,768 x 64: 101, 147 and 123), and where the
+// exhaustive search would need more scratch.
 Search plan_search(const dc_ctx *ctx, int T, int Na, int Nb, int precision, bool two, bool ordering) {
     switch (ctx ? ctx->debug_search : 0) {
         case DC_DEBUG_ORDERED: return Search::ordered;
         case DC_DEBUG_SCREEN: return Search::screen;
         case DC_DEBUG_EXACT: return Search::exact;
     }
+    const bool bf16 = precision == DC_PREC_BF16_REFINE;
+    if (bf16 && two && Na >= 32768 && (long)T * Na <= 1 << 17 && Nb >= 32 && Nb <= 128)
+        return Search::screen;
     if (ordering && ordered_pays(T, Na, Nb, two)) return Search::ordered;
-    if (precision == DC_PREC_BF16_REFINE &&
-        ((Na >= 8192 && (long)T * Na <= 65536) ||
-         search_scratch_bytes(Search::exact, T, Na, Nb) > screen_scratch_bytes(T, Na, Nb)))
+    if (bf16 &&
+        search_scratch_bytes(Search::exact, T, Na, Nb) > screen_scratch_bytes(T, Na, Nb))
         return Search::screen;
     return Search::exact;
 }

@@ -1568,23 +1568,37 @@ bool order_is_small(int Na, int Nb) { return std::max(Na, Nb) <= ORD_SMALL; }
 
 }  // namespace
 
-// Where this search is the fastest, measured over 1 to 4,096 frames of 32 to 65,536 points (us, the
-// exact search / the bf16 screen / this one, for both directions).  64 frames of 64 x 64: 32 / 82 /
-// 26, of 1,024 x 1,024: 77 / 109 / 37, of 8,192 x 8,192: 766 / 414 / 121.  Ordering costs as much
-// as a few hundred targets do, so a handful of points against many is left to the exact search:
-// 100 frames of 32,768 x 64: 213 / 814 / 315, of 32,768 x 512: 410 / 869 / 361; but on one or a few
-// frames the exact search leaves the chip idle: one frame of 8,192 x 128: 108 / 95 / 60.  One
-// direction: 64 frames of 256 x 256: 25 / 72 / 26, of 1,024 x 1,024: 42 / 73 / 34; few queries
-// against many targets gain least (one frame of 512 x 32,768: 66 / 260 / 81; 100: 497 / 322 / 236).
-// (The ordered search's times where it is not taken are from before its blocks were screened.)
+// Where this search is the fastest, measured over 1 to 4,096 frames of 16 to 65,536 points, 1,968 calls on
+// clouds of a sheet (us, ordered / bf16 screen / every pair).  No call is slower than the search that its
+// precision had without this one (noise aside); the least of the three is missed by 1.2% on average in one
+// direction, by nothing in both (at most by 20%, 256 frames of 16 x 32: 27 / 91 / 32).
+//
+// Both directions: nearly everywhere (64 frames of 64 x 64: 24 / 82 / 28; 1,024 of 16 x 2,048: 151 / 297 /
+// 647).  Every pair is faster for many rows that fill the chip against few targets, the line rising with the
+// rows of a frame (256 frames of 2,048 x 128: 74 / 192 / 60, 64 of 8,192 x 256: 83 / 194 / 75, 16 of 65,536 x 384:
+// 169 / 350 / 155), for 16 targets of many frames or of rows by the ten thousand, and for a handful of rows
+// against targets by the ten thousand (16 frames of 64 x 65,536: 209 / 670 / 160).
+//
+// One direction (a to b): ordering both clouds for one search pays with targets by the hundred and rows enough
+// for them (4 frames of 512 x 384: 24 / 69 / 26; 1,024 of 512 x 256: 78 / 178 / 61; one of 2,048 x 65,536: 83 / 470 /
+// 72; 4 of them: 80 / 486 / 152), for fewer targets where rows fill the chip, and, on few frames, for 1,024
+// to 4,096 targets, which the exhaustive search walks in a chain (one frame of 16 x 2,048: 30 / 47 / 55).
 bool ordered_pays(int T, int Na, int Nb, bool two) {
-    const int lo = std::min(Na, Nb), hi = std::max(Na, Nb);
-    const bool few = (long)T * hi <= 65536;
-    if (two)
-        return lo >= 512 || (lo >= 256 && hi / 64 <= lo) || (lo >= 64 && hi / 8 <= lo) ||
-               (lo >= 128 && few);
-    return (Na >= 512 && Nb >= 256 && Nb / 64 < Na) ||
-           (few && Na >= 8192 && Nb >= 64 && Nb / 8 < Na);
+    const long rows = (long)T * Na;
+    if (two) {
+        const int few = Na < 384    ? 16
+                        : Na < 2048 ? 32
+                                    : std::min(std::max(128, Na / 32),
+                                               std::max(256, std::min(Na / 64, 512)));
+        if (rows >= 1 << 18 && Nb <= few) return false;
+        if ((T >= 256 && Nb <= 16) || Nb <= Na / 1024) return false;
+        if (Nb >= 16384 && (Na <= Nb / 1024 || (T >= 4 && Nb >= 32768 && Na <= Nb / 340))) return false;
+        return (long)Na * Nb > 512;
+    }
+    return (Nb >= (T < 256 ? 384 : 512) && Na >= 384 && (Nb / 16 <= Na || (rows >= 8192 && Nb / 48 <= Na))) ||
+           (Nb >= 192 && Na >= 1024 && T >= 256) ||
+           (Na >= 8192 && Nb >= (rows <= 1 << 19 ? 64 : 256)) ||
+           (T <= 64 && Nb >= 1024 && Nb <= 4096);
 }
 
 size_t ordered_scratch_bytes(int T, int Na, int Nb) {

@@ -40,3 +40,16 @@ def test_queries_the_screen_cannot_settle():
     F = [sweep._frame("beyond", r, n, m) for _ in range(T)]
     st = _stats(p, np.stack([f[0] for f in F]), np.stack([f[1] for f in F]), reduction=1, b_side=False)
     assert st["queries"] == st["fallbacks"] == T * n
+
+
+# few rows against a few thousand targets, one frame and many; the screen's own calls; exhaustive ones
+@pytest.mark.parametrize("T,n,m,two,counted", [(1024, 16, 2048, True, True), (256, 384, 8192, False, True),
+                                               (1, 16, 2048, False, True), (1, 40000, 64, True, True),
+                                               (1024, 512, 256, False, False), (64, 20000, 16, True, False)])
+def test_searches_taken(T, n, m, two, counted):
+    """The searches of bf16 calls by what they count: every pair evaluated counts no queries."""
+    p = gpu()
+    r = np.random.default_rng(3)
+    A, B = (r.uniform(-.5, .5, (T, k, 3)).astype(np.float32) for k in (n, m))
+    st = _stats(p, A, B, **({} if two else dict(reduction=1, b_side=False)))
+    assert st["queries"] == (T * (n + m if two else n) if counted else 0)

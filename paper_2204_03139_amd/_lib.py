@@ -127,10 +127,14 @@ def _check(rc: int, where: str):
 # its kernels.  So streams and pointers are passed as plain integers, and the current stream is read
 # without the torch.cuda.Stream object around it, whose per-thread state is built anew in every
 # backward (autograd's thread).  One step of 1 x 2,048 points: 215 us before, 166 us now.
+# That read is no part of torch's public interface: where a torch has it not, the object is made.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream(stream=None):
-    if stream is not None:
-        return stream.cuda_stream
-    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    if stream is None and _raw_stream is not None:
+        return _raw_stream(torch.cuda.current_device())
+    return (torch.cuda.current_stream() if stream is None else stream).cuda_stream
 
 
 def _ptr(t, dtype, shape=None, name="tensor"):

@@ -862,8 +862,11 @@ constexpr float NEAR_SAFE = 1e30f;  // |q'|^2 and v up to which nothing overflow
 // that shows where few frames run beside it: a query takes about 4 us, a sweep of the blocks as long as
 // the tests of their boxes, so the line lies at NEAR_FEW and one query more per 256 blocks.  Two frames
 // of 131,072 points take 181 us with it, 268 us with three queries at any size; one frame of 262,144
-// points 264 and 302 us (ordering included, both directions).
-constexpr int NEAR_FEW = 3;
+// points 264 and 302 us (ordering included, both directions).  It ends at NEAR_FEW_MOST more: the waves of
+// larger clouds fill the chip, and past half of the queries the sweep is the less work (one frame of
+// 1,048,576 points in 27 clumps 3.65 -> 2.45 ms; 524,288 targets on a sphere about the queries, whose blocks
+// are all in reach of each, 738 -> 73 ms; of 4,194,304 and 16,777,216 points in one sheet no change).
+constexpr int NEAR_FEW = 3, NEAR_FEW_MOST = 32;
 
 // Adds n to a counter: 0 queries, 1 sub-tiles read again, 2 queries searched again.
 __device__ __forceinline__ void near_count(const NearParams &pr, int lane, int which, unsigned long long n) {
@@ -1370,7 +1373,7 @@ __device__ __forceinline__ void near_body(const NearParams &pr, const Blk &blk) 
         // meet their minimum more than once, and searched one by one for it one frame of 262,144 points
         // took 168 ms, settled here 25 ms (20 frames of 65,536: 43.6 and 20.7; the exhaustive fp32 search
         // 11.4 and 10.9).
-        if (!screened || __popcll(again) > NEAR_FEW + nblk / 256) {
+        if (!screened || __popcll(again) > NEAR_FEW + min(nblk / 256, NEAR_FEW_MOST)) {
             // the block of the least screened value is known once its other half is, too: otherwise each
             // query would stop the sweep there
             int done = -1;

@@ -47,9 +47,11 @@ extern "C" {
 #define DC_ERR_DEGENERATE (-5) /* a frame's total surface area is zero or not finite */
 #define DC_ERR_UNSUPPORTED (-6)/* a valid request the library cannot run (serving program) */
 
-/* precision of the nearest-neighbour search (both give the same indices and distances).  Either
- * searches spatially ordered clouds, ruling most pairs out by bounding boxes, wherever that is the
- * faster way; elsewhere every pair is evaluated as below. */
+/* precision of the nearest-neighbour search: both give the indices and distances of the exact
+ * single-precision search, bit for bit.  Either searches spatially ordered clouds wherever that is
+ * the faster way: most pairs are ruled out by bounding boxes, of the others, where there are queries
+ * enough, those that a bf16 matrix-core screen cannot rule out within the bound of its error are
+ * evaluated in single precision.  Elsewhere every pair is evaluated as below. */
 #define DC_PREC_FP32 0        /* exact single-precision search on the vector ALUs */
 #define DC_PREC_BF16_REFINE 1 /* bf16 matrix-core screen, certified, exact fp32 re-evaluation, where
                                * it is faster than the exact search */

@@ -79,6 +79,7 @@ int arena_reserve(dc_ctx *ctx, size_t bytes, size_t plain, hipStream_t s) {
         DC_HIP(hipStreamWaitEvent(s, ctx->arena_ev, 0));
     Arena &a = ctx->arena;
     a.reset();
+    const bool spare = plain < bytes;  // the call can do with less
     plain = std::max(ctx->arena_plain, std::min(plain, bytes));
     if (bytes <= a.cap) {
         ctx->arena_plain = plain;
@@ -101,8 +102,8 @@ int arena_reserve(dc_ctx *ctx, size_t bytes, size_t plain, hipStream_t s) {
         return DC_ERR_NOMEM;
     }
     size_t left = 0, all = 0;
-    DC_HIP(hipMemGetInfo(&left, &all));
-    if (want > left + a.cap) {
+    if (spare) DC_HIP(hipMemGetInfo(&left, &all));
+    if (spare && want > left + a.cap) {
         set_error("device allocation of " + std::to_string(want) + " bytes failed");
         return DC_ERR_NOMEM;
     }

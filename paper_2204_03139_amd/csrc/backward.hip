@@ -206,10 +206,10 @@ __global__ __launch_bounds__(BW_THREADS) void k_vertex_grad(VertexGradParams p) 
 // the sums run in the same order on every run.
 //
 // Workgroups of 512 threads, four to a compute unit, for up to GP_WIDE items a frame, else of 1,024,
-// two to a compute unit: fewer workgroups then read the keys.  The three kernels of a backward, 512
-// against 1,024 threads: 40 frames of 8,192 points 38 / 55 us (165 us with sorts), 17 frames of
-// 30,011 x 5,003 (both gradients) 69 / 77 (198), 24 frames of 32,768 x 20,011 76 / 91, 100 frames of
-// 65,536 538 / 452 (697).
+// two to a compute unit: fewer workgroups then read the keys.  The kernels of a backward, 512 against
+// 1,024 threads: 40 frames of 8,192 points 40 / 55 us (124 us with sorts), 17 frames of 30,011 x 5,003
+// (both gradients) 69 / 79 (192), 24 frames of 32,768 x 20,011 78 / 92 (158), 100 frames of 65,536
+// 533 / 445 (719).
 constexpr int GP_SMALL = 512, GP_LARGE = 1024;
 constexpr int GP_WIDE = 49152;
 constexpr int GP_IBITS = 17;      // bits of an item in a listed word, below its key

@@ -42,3 +42,21 @@ def test_large(a, b, T, n, m):
     for k in every:
         assert torch.equal(got[k], every[k]), k
     ctx.close()
+
+
+def test_most_frames():
+    """65,535 frames, the most a call takes, of clouds that are ordered."""
+    p = gpu()
+    say("[large] 65535 frames of 40 x 33")
+    g = torch.Generator(device="cuda")
+    g.manual_seed(1)
+    A, B = (torch.rand((65535, k, 3), generator=g, device="cuda") for k in (40, 33))
+    ctx = p.Context(0)
+    out = []
+    for search in (1, 3):
+        ctx.debug_search(search)
+        out.append(p.chamfer_fwd(A, B, ctx=ctx))
+    torch.cuda.synchronize()
+    for k in out[0]:
+        assert torch.equal(out[0][k], out[1][k]), k
+    ctx.close()

@@ -38,8 +38,8 @@ VECTOR_ISSUE_PEAK = CUS * SIMDS_PER_CU * PEAK_CLOCK_HZ / 2
 # profiles/k_near_grid100_65536pts_100frames_counters.md); valid only for the machine code they were
 # taken on (sha256 of the kernel's bytes in the built library's gfx950 code object).
 NEAR_SYMBOL = "_ZN2dc12_GLOBAL__N_16k_nearENS0_10NearParamsE"
-NEAR_COUNTERS = dict(code_sha256="d5daaaec35d73b24e914ae6acdebd4b1609fa514a95da2f9def0ca6c7603a0e6", vector_insts=693802000, mfma_insts=8187720,
-                     bytes=122843 * 1024 * 2 + 136195 * 1024)
+NEAR_COUNTERS = dict(code_sha256="b38eee3f80d95c60ef088d04c187e15e0839bbd42223140e1459990e46017b4e", vector_insts=694342000, mfma_insts=8187400,
+                     bytes=130500 * 1024 * 2 + 194035 * 1024)
 MFMA_FLOPS = 2 * 32 * 32 * 16     # of one v_mfma_f32_32x32x16_bf16
 LIB = os.path.join(os.path.dirname(os.path.abspath(__file__)), "paper_2204_03139_amd",
                    "libdiffcloud.so")

@@ -21,15 +21,16 @@
 // again for the smallest canonical distance and its smallest original index; a lane that has more of
 // them than it remembers, or in k_near_shared met its minimum in two sub-tiles, is searched again.  A
 // box of zero size holds one point repeated: its distance and least index stand for the whole block.
+// Points with a NaN coordinate are in no box: they are no targets, and queries of their own kind.
 //
-// What it costs and what bounds it (100 frames of 65,536 x 65,536, both directions).  k_near: 1.22 ms.  A
-// wave screens 21 of 2,048 blocks (690 of 65,536 pairs per query; the least possible for these blocks
-// is 17 to 21) in 3,450 vector instructions; the waits of six waves per SIMD bound it as much as
+// What it costs and what bounds it (100 frames of 65,536 x 65,536, both directions).  k_near: 1.20 ms.  A
+// wave screens 20 of 2,048 blocks (640 of 65,536 pairs per query; the least possible for these blocks
+// is 17 to 21) in 3,390 vector instructions; the waits of six waves per SIMD bound it as much as
 // their issue.  With the blocks evaluated, at 6.5 instructions per pair and 6,500 per wave, it took
 // 1.72 ms, bound by vector issue; the exhaustive searches of the same frames 53.9 ms (fp32) and
 // 25.2 ms (bf16 screen and its refine).  Targets on a sphere about all queries, where no box rules
-// anything out, are the exhaustive searches' to win (20 frames: 17 ms; 11 ms with the blocks
-// evaluated).  Ordering: 0.28 ms, of which 0.17 ms deals out the points, 13 million 16-byte stores
+// anything out and the screen settles nothing, are the exhaustive fp32 search's to win (20 frames: 20.7 ms
+// against 10.9; the bf16 screen took 37 to 69).  Ordering: 0.28 ms, of which 0.17 ms deals out the points, 13 million 16-byte stores
 // at random inside a cloud's megabyte.  On one frame a wave's chain of dependent loads bounds it: 106
 // us, 56 us with four waves to a query wave.
 #include <algorithm>

@@ -215,6 +215,7 @@ constexpr int GP_WIDE = 49152;
 constexpr int GP_IBITS = 17;      // bits of an item in a listed word, below its key
 constexpr int GP_MAX = 1 << GP_IBITS;
 constexpr float GP_HEAVY = 12.f;
+constexpr int GP_LONG = 16;       // most keys of a round that are listed thread by thread
 
 // items listed at once, and most keys, of a workgroup of TH threads
 template <int TH>
@@ -226,14 +227,20 @@ struct GroupLds {
     int start[gp_cap<TH>() + 4];  // first position of each key's items, over the workgroup's range
     union {
         struct {
-            int cursor[gp_cap<TH>()];
-            unsigned listed[gp_cap<TH>()];
-            int item[gp_cap<TH>()];  // the items, by key and then in increasing order
+            union {
+                struct {
+                    int cursor[gp_cap<TH>()];
+                    unsigned listed[gp_cap<TH>()];
+                };
+                unsigned short own[GP_LONG][TH];  // of long keys: the threads' items, then their places
+            };
+            int item[gp_cap<TH>()];  // the items, by key and then in a fixed order
         };
         float row[3][gp_cap<TH>()];  // in their place, what the items stand for
     };
     int wsum[TH / 64];
     int heavy;  // the first heavy key of a round; before the rounds: whether there is one
+    int some_long;  // whether there are keys of which a list holds no more than GP_LONG
     double part[TH / 64][9];
 };
 
@@ -290,10 +297,12 @@ struct Row3 {
 // of a wave's lanes wait for its longest key, and two keys in hand to fill the waits spilled registers
 // (Chamfer backward of 100 x 65,536 points 256 -> 191 us, of 40 x 8,192 18.2 -> 12.7 us).
 //
-// A heavy key has a round and the whole workgroup for itself: its items listed thread by thread, or, where
-// they are more than fit, straight from the keys, each thread its every TH-th item.  20 of 19,602 faces with
-// all of a frame's 65,536 points take 350 us, ranked like the others 4,460 us.  Rounds for ranges without
-// one (HEAVY false) are compiled by themselves: in common code the other branch's registers spilled.
+// A heavy key has a round and the whole workgroup for itself.  Its items, and those of a round of few long
+// keys, are listed thread by thread: each thread counts its own, and puts them behind those of the threads
+// before.  (More items than fit are summed straight from the keys, each thread its every TH-th.)  20 of 19,602
+// faces with all of a frame's 65,536 points take 435 us, ranked like the others 4,460 us; 200 of them in 40
+// frames 0.87 and 1.33 ms.  Rounds for ranges
+// without such keys (HEAVY false) are compiled by themselves: in common code the others' registers spilled.
 template <int TH, int M, bool STAGE, bool HEAVY, class Own, class Fetch, class Each, class Put>
 __device__ __forceinline__ void sum_rounds(const int32_t *__restrict__ keys, int n, int k0, int nk, int G,
                                            GroupLds<TH> &s, const Own &own, const Fetch &fetch,
@@ -327,21 +336,39 @@ __device__ __forceinline__ void sum_rounds(const int32_t *__restrict__ keys, int
         }
         const int total = s.start[ke] - base;
         const bool over = HEAVY && total > CAP, listed = total > 0 && !over;
-        if (listed && heavy) {
-            int mine = 0;
-            each_key<TH>(keys, n, [&](int, int key) { mine += key == k0 + kb ? 1 : 0; });
-            int at = mine;
-#pragma unroll
-            for (int off = 1; off < 64; off <<= 1) {
-                const int o = __shfl_up(at, off, 64);
-                if (lane >= off) at += o;
-            }
-            if (lane == 63) s.wsum[wave] = at;
+        // few long keys: comparing their items would take longer than two more passes over the keys
+        const bool by_thread = HEAVY && listed && ke - kb <= GP_LONG &&
+                               heavy_key(total, n * (ke - kb));
+        if (by_thread) {
+            const int keys_now = ke - kb;
+            for (int k = 0; k < keys_now; ++k) s.own[k][tid] = 0;
+            each_key<TH>(keys, n, [&](int, int key) {
+                const unsigned k = key - k0 - kb;
+                if (k < (unsigned)keys_now) ++s.own[k][tid];
+            });
             __syncthreads();
-            at -= mine;
-            for (int w = 0; w < wave; ++w) at += s.wsum[w];
+            for (int k = wave; k < keys_now; k += WAVES) {  // counts to places, a wave a key
+                constexpr int PER = TH / 64;
+                unsigned short *c = &s.own[k][lane * PER];
+                int sum = 0;
+                for (int u = 0; u < PER; ++u) sum += c[u];
+                int at = sum;
+#pragma unroll
+                for (int off = 1; off < 64; off <<= 1) {
+                    const int o = __shfl_up(at, off, 64);
+                    if (lane >= off) at += o;
+                }
+                at += s.start[kb + k] - base - sum;
+                for (int u = 0; u < PER; ++u) {
+                    const int next = at + c[u];
+                    c[u] = (unsigned short)at;
+                    at = next;
+                }
+            }
+            __syncthreads();
             each_key<TH>(keys, n, [&](int i, int key) {
-                if (key == k0 + kb) s.item[at++] = i;
+                const unsigned k = key - k0 - kb;
+                if (k < (unsigned)keys_now) s.item[s.own[k][tid]++] = i;
             });
             __syncthreads();
         } else if (listed) {
@@ -441,7 +468,7 @@ __device__ __forceinline__ void grouped_sums(const int32_t *__restrict__ keys, i
     constexpr int CAP = gp_cap<TH>();
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     for (int k = tid; k < nk; k += TH) s.cursor[k] = 0;
-    if (tid == 0) s.heavy = 0;
+    if (tid == 0) s.heavy = s.some_long = 0;
     __syncthreads();
     each_key<TH>(keys, n, [&](int i, int key) {
         const int k = key - k0;
@@ -459,6 +486,7 @@ __device__ __forceinline__ void grouped_sums(const int32_t *__restrict__ keys, i
             most = max(most, c[u]);
         }
         if (heavy_key(most, n)) s.heavy = 1;
+        if (most >= CAP / GP_LONG) s.some_long = 1;
         int incl = sum;
 #pragma unroll
         for (int off = 1; off < 64; off <<= 1) {
@@ -478,7 +506,7 @@ __device__ __forceinline__ void grouped_sums(const int32_t *__restrict__ keys, i
         if (tid == TH - 1 && nk == CAP) s.start[nk] = at;
         __syncthreads();
     }
-    if (s.heavy)
+    if (s.heavy || (s.some_long && s.start[nk] > CAP))
         sum_rounds<TH, M, STAGE, true>(keys, n, k0, nk, G, s, own, fetch, each, put);
     else
         sum_rounds<TH, M, STAGE, false>(keys, n, k0, nk, G, s, own, fetch, each, put);
